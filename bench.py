@@ -36,7 +36,7 @@ CSRC = os.path.join(ROOT, "paper_1307_4703_amd", "csrc")
 # sources of the dominant kernel (the two-step pass); the counters in
 # profiles/traffic.json hold for the hash of these files
 KERNEL_SRC = [os.path.join(CSRC, f)
-              for f in ("gg_device.h", "gg_node.h", "gg_fused.hip", "gg_cde.hip")]
+              for f in ("gg_device.h", "gg_node.h", "gg_fused.hip", "gg_pipe.hip", "gg_cde.hip")]
 
 
 def log(msg):
@@ -164,8 +164,8 @@ def time_lattice(name, steps, warmup, tile, chunk, form=None, monitor_every=1024
         lat.set_two_step(form["fuse"], form["rows"])
         form["layout"] = lat.layout
         # graph chunk of the timed region: whole replays inside it (a
-        # multiple of 4 steps, of 8 with the four-step pass)
-        q = 8 if form["fuse"] == 5 else 4
+        # multiple of 4 steps, with fuse 5 of a pair of its passes)
+        q = 2 * lat.step_profile(0)["steps_per_pass"] if form["fuse"] == 5 else 4
         chunk_t = min(chunk, steps // q * q) if chunk > 0 else 0
         lat.set_launch(form["tile"][0], form["tile"][1], chunk_t)
         log(f"{wl.name}: {wl.nx}x{wl.ny}, {nf} fluid nodes, storage {wl.storage}, "
@@ -238,7 +238,7 @@ def roofline(r, storage, traffic):
         # by the passes they hold (the boundary tiles' kernel runs beside)
         ms = (p["ms_pass"] + p["ms_graph"]) / passes
         units = spp * p["pass_fluid"]
-        kind = ("four-step pass (interior tiles)" if spp == 4 else
+        kind = (f"{'four' if spp == 4 else 'eight'}-step pass" if spp > 2 else
                 "two-step pass (interior tiles)" if p["fuse"] != 4 else "two-step pass")
         n_launch = passes
     else:
@@ -522,11 +522,13 @@ def counters_leg(leg, tile, chunk_unused=0):
             lat.close()
             seg = "true" if p["fuse"] == 4 else "false"
             spp = p["steps_per_pass"]
-            # rows + 2 wavefronts per tile, rows + 6 in the four-step pass
-            waves = p["rows"] + (6 if spp == 4 else 2)
+            # rows + 2 wavefronts per tile, a wavefront per step in the
+            # passes of four and eight
+            waves = spp if spp > 2 else p["rows"] + 2
             grid = 8 * ((p["pass_tiles"] + 7) // 8) * waves * 64
-            kern = "k_tile4" if spp == 4 else "k_tile2"
-            manifest[name] = {"kernel": f"{kern}<{CTYPE[wl.storage]}, {seg}, {p['rows']},",
+            kern = (f"k_pipe<{CTYPE[wl.storage]}, {spp}," if spp > 2 else
+                    f"k_tile2<{CTYPE[wl.storage]}, {seg}, {p['rows']},")
+            manifest[name] = {"kernel": kern,
                               "grid": grid, "units": spp * p["pass_fluid"],
                               "bytes_per_update": bytes_per_update(wl.storage)}
             log(f"counters: {name} {manifest[name]}")
@@ -534,15 +536,15 @@ def counters_leg(leg, tile, chunk_unused=0):
         wls = W.batch_instances(64, 4703)
         lats = [Lattice.from_workload(wl, storage="f32") for wl in wls]
         # the form the library's autotuner picks for this batch on this GPU
-        # (four-step passes, the boundary tiles apart): both kernels of
+        # (eight-step passes, the boundary strips apart): both kernels of
         # each pass, their bytes summed per pass
         b = Batch(lats, tile=(64, 4), graph_chunk=0, fuse=5, rows=6)
         b.step(16)
         torch.cuda.synchronize()
         b.close()
         nf = sum(l.info()["n_fluid"] for l in lats)
-        manifest["batch64"] = {"kernel": "k_tile4<float,", "grid": None, "sum_kernels": True,
-                               "units": 4 * nf, "bytes_per_update": bytes_per_update("f32")}
+        manifest["batch64"] = {"kernel": "k_pipe<float, 8,", "grid": None, "sum_kernels": True,
+                               "units": 8 * nf, "bytes_per_update": bytes_per_update("f32")}
     elif leg == "adjoint":
         wl = workload("gg2048_f32")
         weight, target, r_box = W.chamber_misfit_setup(wl)

@@ -271,14 +271,14 @@ gg_status gg_load(gg_lattice *lat, const void *buf, size_t nbytes);
  * (one work-group each, tile_x * tile_y in {64, 128, 256, 512}, tile_x a
  * multiple of 8); only tiles holding a fluid node are launched.
  * graph_chunk > 0 replays gg_step in HIP graphs of that many steps (rounded
- * up to even, to a multiple of 4 with the two-step pass, of 8 with fuse =
- * 5); 0 launches every step. */
+ * up to even, to a multiple of 4 with the two-step pass, of 8 or 16 with fuse
+ * = 5 and passes of four or eight steps); 0 launches every step. */
 gg_status gg_set_launch(gg_lattice *lat, int32_t tile_x, int32_t tile_y,
                         int32_t graph_chunk);
 
 /* Two-step pass (fuse = 2, 3 or 4; a new lattice starts with fuse = 3,
- * strip_h = 6), four-step pass (fuse = 5) or single steps only (fuse =
- * 1). The pass reads the state
+ * strip_h = 6), pass of four or eight steps (fuse = 5) or single steps only
+ * (fuse = 1). The pass reads the state
  * of an even step once and writes the state two steps later into a second
  * set of population planes (same size as the first; allocated while
  * fuse >= 2, freed by fuse = 1), so every population crosses HBM once per
@@ -293,13 +293,16 @@ gg_status gg_set_launch(gg_lattice *lat, int32_t tile_x, int32_t tile_y,
  *     strips and tiles that touch a segment run in a kernel of their own,
  *     beside the others on a second stream, which keeps the boundary code
  *     out of the others' register budget);
- *   fuse = 5: runs of 8k steps from an even step in passes of four steps
- *     (temporal blocking over the AA pairs of steps, collide-and-stream
- *     after Eq. 7 four times per trip through memory): one work-group of
- *     12 wavefronts per tile of 58 columns x 6 rows with a three-node halo,
- *     each step's row-crossing populations through LDS; the tiles whose
- *     nodes within two of their own link to a segment run as 58 x 2 tiles
- *     in a kernel of their own on the second stream, as with fuse = 3.
+ *   fuse = 5: runs of 4k steps from an even step in pairs of passes of four
+ *     steps, or, for FP32 lattices beyond the Infinity Cache (from 2M fluid
+ *     nodes), of eight (temporal blocking over the AA pairs of steps,
+ *     collide-and-stream after Eq. 7 that many times per trip through
+ *     memory), the last steps of a run in shorter ones: one work-group of a
+ *     wavefront per step walks a strip of 58 (50) columns row by row, each
+ *     wavefront two rows behind the one of the step before and taking its
+ *     rows from LDS; the library picks the strips' height, and whether the
+ *     strips that link to a segment run in the one kernel with the others
+ *     (small lattices) or in a kernel of their own on the second stream.
  *     Other runs step as with fuse = 3 (strip_h 6 or 14). Lattices without
  *     pressure segments or the paper's walls, periodic axes of 4 nodes or
  *     more; otherwise fuse = 5 steps as fuse = 3. The
@@ -436,11 +439,9 @@ gg_status gg_batch_form(const gg_batch *batch, int32_t *tile_x, int32_t *tile_y,
 /* Two-step pass for the batch (see gg_set_two_step): fuse 3 or 4 with
  * tiles of rows = 6 or 14 rows, over the members' tiles in one flat list
  * (fuse 3: the boundary tiles of all members in a second list on a second
- * stream); fuse 5: four-step passes over the members' 58 x 6 tiles (the
- * boundary tiles apart), runs of 8k + 4 steps ending in two two-step
- * passes of fuse 3's form with `rows` rows (GG_ERR_ARG for a member with a
- * periodic axis under 4 nodes); fuse = 1 goes back to
- * single steps. Every member must have its
+ * stream); fuse 5: passes of four or eight steps over the members' strips
+ * (chosen for the members' fluid nodes together), GG_ERR_ARG for a member
+ * with a periodic axis under 4 nodes; fuse = 1 goes back to single steps. Every member must have its
  * second plane set (fuse >= 2 on the member, the default) and all members
  * must sit at steps of one parity (else GG_ERR_STATE). The states advance
  * exactly as with single steps. */
@@ -559,8 +560,9 @@ gg_status gg_monitor_read(gg_lattice *lat, gg_diag *out, int64_t *count);
  * most HBM traffic: the kernel over the interior tile list of each two-step
  * pass (with fuse 2 and 3 the boundary tiles run in a second kernel beside
  * it on a side stream; with fuse 4 it is the pass's only kernel), of each
- * four-step pass where fuse 5 runs them (two-step passes of leftover steps
- * are then counted apart, in n_pass2), or the step kernel of each single
+ * pass of four or eight steps where fuse 5 runs them (one kernel, or on
+ * large lattices with its boundary strips' kernel beside it; the shorter
+ * passes of leftover steps are then counted apart, in n_pass2), or the step kernel of each single
  * step. */
 typedef struct gg_profile {
   double ms_total;          /* HIP events around the whole call */
@@ -581,13 +583,16 @@ typedef struct gg_profile {
                                rows + 2 wavefronts each, 8 * ceil(tiles / 8)
                                work-groups launched) */
   int64_t pass_side_tiles;  /* tiles of the side kernel (2 rows each) */
-  int64_t n_pass2;          /* with the four-step pass: plain launches of the
-                               two-step passes of leftover steps (their
-                               interior kernel), and */
+  int64_t n_pass2;          /* with passes of four or eight steps: plain
+                               launches of the shorter passes of leftover
+                               steps, in pairs of steps (a four-step one
+                               counts as two), and */
   double ms_pass2;          /* their summed duration */
   int32_t fuse, rows;       /* launch form used (fuse 1: single steps only) */
-  int32_t steps_per_pass;   /* 2, or 4 where the four-step pass runs (fuse
-                               5; its tiles are then the pass_ fields') */
+  int32_t steps_per_pass;   /* 2, or 4 or 8 where fuse 5's passes run (their
+                               strips are then the pass_ fields' tiles, one
+                               work-group of steps_per_pass wavefronts each,
+                               and rows the strips' height) */
 } gg_profile;
 
 /* Instrumentation: gg_step(lat, n) with a pair of HIP events recorded on

@@ -91,6 +91,8 @@ inline CollK<T> make_collk(double omega_f, double omega_g, double wg_axis, doubl
 
 // Tile flag: some node of the tile has a link into a boundary segment.
 constexpr int TILE_TOUCHES_SEGMENT = 1;
+// Pipeline strips: some node the strip computes has a non-fluid neighbour.
+constexpr int TILE_HAS_LINKS = 2;
 
 // One launched tile: lattice (instance) index, origin, flags.
 struct Tile {

@@ -41,12 +41,18 @@ hipError_t launch_tile2(gg_storage s, bool pairs, bool seg, int rows, const LatD
                         const Tile *tiles, int n_tiles, int dir, int dt, hipStream_t st,
                         bool press = false, void *tape0 = nullptr, void *tape1 = nullptr);
 
-// Four steps in one pass (t even, natural order in and out): one work-group
-// of rows + 6 wavefronts per tile of 58 columns x (flags >> 8) rows, rows 2
-// (seg, the boundary kernel) or 6; no pressure segments; dir and dt as for
-// launch_tile2.
-hipError_t launch_tile4(gg_storage s, bool pairs, bool seg, const LatDesc *d, const Tile *tiles,
-                        int n_tiles, int dir, int dt, hipStream_t st);
+// ns steps in one pass (natural order in and out) through the kernel made
+// for max_steps, ns = 2..max_steps: one work-group of max_steps wavefronts
+// per strip of 64 - 2 (max_steps - 1) columns x (flags >> 8) rows, a
+// wavefront per step; seg_tiles: the strips whose segment bit is set (the
+// kernel then carries the boundary rules), launched before the others; no
+// pressure segments; dir and dt as for launch_tile2.
+hipError_t launch_pipe(gg_storage s, bool pairs, int max_steps, const LatDesc *d,
+                       const Tile *seg_tiles, int n_seg, const Tile *tiles, int n_tiles, int dir,
+                       int dt, int ns, hipStream_t st);
+// Work-groups of launch_pipe's kernel (with the boundary rules: seg) that the
+// GPU holds at once, and its CUs.
+int pipe_slots(gg_storage s, bool pairs, int max_steps, bool seg, int *cus);
 
 // Compound-only step on frozen velocity fields (64 x 4 tiles, 256-thread
 // work-groups, XCD-aware tile order as launch_step); odd = parity of the

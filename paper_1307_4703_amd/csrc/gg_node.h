@@ -69,6 +69,32 @@ template <> struct DK<float> {
   static __device__ __forceinline__ const GG_CONST CollK<float> &ck(CDesc &L) { return L.ck_f; }
 };
 
+// What the collision of a node reads of its lattice. The functions below
+// take it by reference: from the descriptor as they go (NodeK<T>(L): scalar
+// loads where each value is used), or, in a kernel that collides row after
+// row, held in scalar registers (hold) so that no row waits for loads of
+// the descriptor.
+template <class T> struct NodeK {
+  T rho0, cs, kdec, wga;
+  CollK<T> k;
+  bool has_source;
+  __device__ __forceinline__ explicit NodeK(CDesc &L)
+      : rho0(DK<T>::rho0(L)), cs(DK<T>::cs(L)), kdec(DK<T>::kdec(L)), wga(DK<T>::wga(L)),
+        has_source(L.has_source != 0) {
+    const GG_CONST CollK<T> &c = DK<T>::ck(L);
+    k.f_omc = c.f_omc; k.f_k0 = c.f_k0; k.f_ka = c.f_ka; k.f_kd = c.f_kd;
+    k.f_k3a = c.f_k3a; k.f_k3d = c.f_k3d;
+    k.g_omc = c.g_omc; k.g_k0 = c.g_k0; k.g_ka = c.g_ka; k.g_ki = c.g_ki; k.g_w0 = c.g_w0;
+    k.g_pad = T(0);
+  }
+  __device__ __forceinline__ void hold() {
+    T *v[] = {&rho0, &cs, &kdec, &wga, &k.f_omc, &k.f_k0, &k.f_ka, &k.f_kd, &k.f_k3a, &k.f_k3d,
+              &k.g_omc, &k.g_k0, &k.g_ka, &k.g_ki, &k.g_w0};
+#pragma unroll
+    for (int i = 0; i < 15; ++i) asm volatile("" : "+s"(*v[i]));
+  }
+};
+
 // e_i . u for direction i (paper Eq. 3 velocities), written out per
 // direction: the same value as e_x u_x + e_y u_y, without the products by
 // zero and one that IEEE arithmetic would otherwise have to carry out (the
@@ -231,21 +257,34 @@ __device__ __forceinline__ bool src_solid(uint8_t lc, int j) { return (lc >> (OP
 __device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// 1 / x, correctly rounded. In FP32 the hardware's approximation and one
+// Newton step give the correctly rounded value wherever the approximation is
+// a normal number (x with a biased exponent of 1..252; compared with the
+// division over all 2^32 patterns); a wavefront with any other x divides.
+// 4 instructions on the way instead of the division's 10.
+__device__ __forceinline__ float inverse(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  float y = __builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r);
+  if (__builtin_expect(__any(!__builtin_isnormal(r)), 0)) y = 1.0f / x;
+  return y;
+}
+__device__ __forceinline__ double inverse(double x) { return 1.0 / x; }
+
 // Density and velocity of the fluid at a node from its deviations df
 // (paper Eq. 7, sum over i = 0..8): rho = rho0 + sum df_i; the rest part
 // w_i rho0 carries no momentum.
 template <class T>
-__device__ __forceinline__ void node_velocity(CDesc &L, const T *f, T &rho, T &drho, T &ux,
+__device__ __forceinline__ void node_velocity(const NodeK<T> &N, const T *f, T &rho, T &drho, T &ux,
                                               T &uy) {
 #pragma clang fp contract(off)
   // the populations moving in +x and in -x, shared by rho and j_x
   const T a = (f[1] + f[5]) + f[8];
   const T b = (f[3] + f[6]) + f[7];
   drho = ((f[0] + f[2]) + f[4]) + (a + b);
-  rho = DK<T>::rho0(L) + drho;
+  rho = N.rho0 + drho;
   const T jx = a - b;
   const T jy = (f[2] - f[4]) + (f[5] - f[7]) + (f[6] - f[8]);
-  const T inv_rho = T(1) / rho;
+  const T inv_rho = inverse(rho);
   ux = jx * inv_rho;
   uy = jy * inv_rho;
 }
@@ -257,20 +296,20 @@ __device__ __forceinline__ void node_velocity(CDesc &L, const T *f, T &rho, T &d
 // directions share every product but the last:
 //   pg_i = (1 - om) g_i + om w_i (dC + C e.u / cs2) + w_i src.
 template <class T>
-__device__ __forceinline__ void compound_collide(CDesc &L, int x, int y, const T *g, T ux, T uy,
-                                                 T *pg) {
+__device__ __forceinline__ void compound_collide(const NodeK<T> &N, CDesc &L, int x, int y,
+                                                 const T *g, T ux, T uy, T *pg) {
 #pragma clang fp contract(off)
-  const GG_CONST CollK<T> &K = DK<T>::ck(L);
+  const CollK<T> &K = N.k;
   const T dC = g[0] + g[1] + g[2] + g[3] + g[4];
-  const T C = DK<T>::cs(L) + dC;
-  T src = -DK<T>::kdec(L) * C;
-  if (L.has_source) {
+  const T C = N.cs + dC;
+  T src = -N.kdec * C;
+  if (N.has_source) {
     const int rx = x - L.r_x0, ry = y - L.r_y0;
     if (rx >= 0 && rx < L.r_w && ry >= 0 && ry < L.r_h)
       src += (T)((const GG_GLOBAL double *)L.R)[ry * L.r_w + rx];
   }
   const T even0 = fmad(K.g_k0, dC, K.g_w0 * src);
-  const T even = fmad(K.g_ka, dC, DK<T>::wga(L) * src);
+  const T even = fmad(K.g_ka, dC, N.wga * src);
   const T oddC = K.g_ki * C;
   const T ox = oddC * ux, oy = oddC * uy;
   pg[0] = fmad(K.g_omc, g[0], even0);
@@ -299,10 +338,10 @@ __device__ __forceinline__ void relax_pair(T omc, T fi, T fo, T e, T k, T r, T r
 // 4.5 rho (e.u)^2), and the odd one, 3 w_i rho e.u; opposite directions
 // share both:  pf_i = (1 - om) f_i + om w_i (even_i +- odd_i).
 template <class T>
-__device__ __forceinline__ void fluid_collide(CDesc &L, const T *f, T rho, T drho, T ux, T uy,
+__device__ __forceinline__ void fluid_collide(const NodeK<T> &N, const T *f, T rho, T drho, T ux, T uy,
                                               T usq, T *pf) {
 #pragma clang fp contract(off)
-  const GG_CONST CollK<T> &K = DK<T>::ck(L);
+  const CollK<T> &K = N.k;
   const T q = fmad(rho, T(-1.5) * usq, drho);
   const T r45 = T(4.5) * rho;
   const T ra = K.f_k3a * rho, rd = K.f_k3d * rho;
@@ -311,6 +350,80 @@ __device__ __forceinline__ void fluid_collide(CDesc &L, const T *f, T rho, T drh
   relax_pair<T>(K.f_omc, f[2], f[4], uy, K.f_ka, ra, r45, q, pf[2], pf[4]);
   relax_pair<T>(K.f_omc, f[5], f[7], ux + uy, K.f_kd, rd, r45, q, pf[5], pf[7]);
   relax_pair<T>(K.f_omc, f[6], f[8], uy - ux, K.f_kd, rd, r45, q, pf[6], pf[8]);
+}
+
+// What a link rule reads of segment s in the phase in force: from the
+// descriptor as it goes (SegRef), or read before and kept (SegHeld).
+template <class T> struct SegRef {
+  CDesc &L;
+  const PhaseNow &ph;
+  int s;
+  __device__ __forceinline__ int kind() const { return L.seg_kind[s]; }
+  __device__ __forceinline__ int nx() const { return L.seg_nx[s]; }
+  __device__ __forceinline__ int ny() const { return L.seg_ny[s]; }
+  __device__ __forceinline__ int holdc() const { return L.seg_holdc[s]; }
+  __device__ __forceinline__ T umax4() const { return SegT<T>::umax4(L, s); }
+  __device__ __forceinline__ T s0() const { return SegT<T>::s0(L, s); }
+  __device__ __forceinline__ T s1() const { return SegT<T>::s1(L, s); }
+  __device__ __forceinline__ T iw2() const { return SegT<T>::iw2(L, s); }
+  __device__ __forceinline__ T cin() const { return SegT<T>::cin(ph, s); }
+};
+template <class T> struct SegHeld {
+  int s_ = -1, kind_ = 0, nx_ = 0, ny_ = 0, holdc_ = 0;
+  T umax4_ = T(0), s0_ = T(0), s1_ = T(0), iw2_ = T(0), cin_ = T(0);
+  // (one round of scalar loads)
+  __device__ __forceinline__ void take(CDesc &L, const PhaseNow &ph, int s) {
+    const SegRef<T> r{L, ph, s};
+    s_ = s;
+    kind_ = r.kind(); nx_ = r.nx(); ny_ = r.ny(); holdc_ = r.holdc();
+    umax4_ = r.umax4(); s0_ = r.s0(); s1_ = r.s1(); iw2_ = r.iw2(); cin_ = r.cin();
+  }
+  __device__ __forceinline__ int kind() const { return kind_; }
+  __device__ __forceinline__ int nx() const { return nx_; }
+  __device__ __forceinline__ int ny() const { return ny_; }
+  __device__ __forceinline__ int holdc() const { return holdc_; }
+  __device__ __forceinline__ T umax4() const { return umax4_; }
+  __device__ __forceinline__ T s0() const { return s0_; }
+  __device__ __forceinline__ T s1() const { return s1_; }
+  __device__ __forceinline__ T iw2() const { return iw2_; }
+  __device__ __forceinline__ T cin() const { return cin_; }
+};
+
+// The value arriving at fluid node (x, y) along direction j, whose source
+// cell x - e_j belongs to the open segment sg: vf, and vg for j < 5, from the
+// populations fj, gj of direction j before the collision, the post-collision
+// ones po, qo sent toward the segment (direction opp(j)) and qj (direction
+// j), and the velocity of the collision. Written for the deviations; w_j =
+// w_opp(j), so the rest parts cancel except where noted.
+template <class T, bool PRESS, class SG>
+__device__ __forceinline__ void open_link(const NodeK<T> &N, const SG &sg, int j, int x, int y,
+                                          T fj, T gj, T po, T qo, T qj, T ux, T uy, T usq, T &vf,
+                                          T &vg) {
+#pragma clang fp contract(off)
+  const T rho0 = N.rho0;
+  const T wgj = N.wga;  // (j >= 1)
+  if (sg.kind() == GG_SEG_INLET) {
+    // moving-wall bounce-back, wall velocity -n u(s) with a parabolic
+    // profile across the segment; anti-bounce-back for C_in
+    const T coord = sg.nx() != 0 ? (T)y : (T)x;
+    const T us = sg.umax4() * (coord - sg.s0()) *
+                 (sg.s1() - coord) * sg.iw2();
+    const T en = (T)(EX[j] * sg.nx() + EY[j] * sg.ny());
+    vf = fmad(T(-6) * (T)WF[j] * rho0 * en, us, po);
+    if (j < 5) vg = fmad(T(2) * wgj, sg.cin() - N.cs, -qo);
+  } else if (PRESS && sg.kind() == GG_SEG_PRESSURE) {
+    // do nothing: the node's own value of step t (the density is set by
+    // the rescaling after the step); the compound alike where it is
+    // held, else zero-gradient as at an outlet
+    vf = fj;
+    if (j < 5) vg = sg.holdc() ? gj : qj;
+  } else {
+    // outflow at the reference density with the node's own u;
+    // the compound leaves with zero gradient
+    const T eu = e_dot_u<T>(j, ux, uy);
+    vf = fmad(T(2) * (T)WF[j] * rho0, fmad(T(4.5) * eu, eu, T(-1.5) * usq), -po);
+    if (j < 5) vg = qj;
+  }
 }
 
 // Collision of fluid node (x, y) with link code lc, from the deviations f, g
@@ -328,25 +441,21 @@ __device__ __forceinline__ void fluid_collide(CDesc &L, const T *f, T rho, T drh
 // register budget and their control flow as it was; without it an open
 // pressure link would take the outlet rule.
 template <class T, bool PRESS = true, class FX = Flux>
-__device__ __forceinline__ void collide_node(CDesc &L, int x, int y, uint8_t lc, bool seg_tile,
-                                             const PhaseNow &ph, const T *f, const T *g, T *pf,
-                                             T *pg, T *in_f, T *in_g, FX &fx, bool count,
+__device__ __forceinline__ void collide_node(const NodeK<T> &N, CDesc &L, int x, int y,
+                                             uint8_t lc, bool seg_tile, const PhaseNow &ph,
+                                             const T *f, const T *g, T *pf, T *pg, T *in_f,
+                                             T *in_g, FX &fx, bool count,
                                              const uint32_t *nbr = nullptr) {
   // Every kernel that advances the lattice inlines this function; the fused
   // multiply-adds are written out and no other contraction is allowed, so
   // each of them rounds exactly the same way whatever code surrounds it.
 #pragma clang fp contract(off)
-  const int nx = L.nx, ny = L.ny, pitch = L.pitch;
-  const T rho0 = DK<T>::rho0(L);
   T rho, drho, ux, uy;
-  node_velocity<T>(L, f, rho, drho, ux, uy);
+  node_velocity<T>(N, f, rho, drho, ux, uy);
   const T usq = fmad(ux, ux, uy * uy);
 
-  fluid_collide<T>(L, f, rho, drho, ux, uy, usq, pf);
-  compound_collide<T>(L, x, y, g, ux, uy, pg);
-  const T cs = DK<T>::cs(L);
-  const T wga = DK<T>::wga(L);
-  const T wg[5] = {T(1) - T(4) * wga, wga, wga, wga, wga};
+  fluid_collide<T>(N, f, rho, drho, ux, uy, usq, pf);
+  compound_collide<T>(N, L, x, y, g, ux, uy, pg);
 
   // Value arriving at x along direction j when x - e_j is not fluid: the
   // bounced population f*(x, opp j) for a wall or closed valve; open
@@ -358,6 +467,7 @@ __device__ __forceinline__ void collide_node(CDesc &L, int x, int y, uint8_t lc,
   for (int j = 0; j < 5; ++j) in_g[j] = pg[OPP[j]];
 
   if (seg_tile && lc != 0) {
+    const int nx = L.nx, ny = L.ny, pitch = L.pitch;
     // (every rule below is written for the deviations; w_j = w_opp(j), so
     // the rest parts cancel except where noted)
 #pragma unroll
@@ -378,28 +488,8 @@ __device__ __forceinline__ void collide_node(CDesc &L, int x, int y, uint8_t lc,
       const int s = code - GG_FIRST_SEGMENT;
       if (!((ph.open >> s) & 1u)) continue;  // closed valve: a wall
       T vf, vg = T(0);
-      if (L.seg_kind[s] == GG_SEG_INLET) {
-        // moving-wall bounce-back, wall velocity -n u(s) with a parabolic
-        // profile across the segment; anti-bounce-back for C_in
-        const T coord = L.seg_nx[s] != 0 ? (T)y : (T)x;
-        const T us = SegT<T>::umax4(L, s) * (coord - SegT<T>::s0(L, s)) *
-                     (SegT<T>::s1(L, s) - coord) * SegT<T>::iw2(L, s);
-        const T en = (T)(EX[j] * L.seg_nx[s] + EY[j] * L.seg_ny[s]);
-        vf = fmad(T(-6) * (T)WF[j] * rho0 * en, us, pf[OPP[j]]);
-        if (j < 5) vg = fmad(T(2) * wg[j], SegT<T>::cin(ph, s) - cs, -pg[OPP[j]]);
-      } else if (PRESS && L.seg_kind[s] == GG_SEG_PRESSURE) {
-        // do nothing: the node's own value of step t (the density is set by
-        // the rescaling after the step); the compound alike where it is
-        // held, else zero-gradient as at an outlet
-        vf = f[j];
-        if (j < 5) vg = L.seg_holdc[s] ? g[j] : pg[j];
-      } else {
-        // outflow at the reference density with the node's own u;
-        // the compound leaves with zero gradient
-        const T eu = e_dot_u<T>(j, ux, uy);
-        vf = fmad(T(2) * (T)WF[j] * rho0, fmad(T(4.5) * eu, eu, T(-1.5) * usq), -pf[OPP[j]]);
-        if (j < 5) vg = pg[j];
-      }
+      open_link<T, PRESS>(N, SegRef<T>{L, ph, s}, j, x, y, f[j], j < 5 ? g[j] : T(0), pf[OPP[j]],
+                          j < 5 ? pg[OPP[j]] : T(0), j < 5 ? pg[j] : T(0), ux, uy, usq, vf, vg);
       const T dm = vf - pf[OPP[j]];
       const T dc = (j < 5) ? vg - pg[OPP[j]] : T(0);
       in_f[j] = vf;
@@ -407,6 +497,81 @@ __device__ __forceinline__ void collide_node(CDesc &L, int x, int y, uint8_t lc,
       if (count) fx.add(s, dm, dc);
     }
   }
+}
+
+// The collision alone: post-collision deviations and the velocity (and its
+// square) it was made with.
+template <class T>
+__device__ __forceinline__ void collide_only(const NodeK<T> &N, CDesc &L, int x, int y, const T *f,
+                                             const T *g, T *pf, T *pg, T &ux, T &uy, T &usq) {
+#pragma clang fp contract(off)
+  T rho, drho;
+  node_velocity<T>(N, f, rho, drho, ux, uy);
+  usq = fmad(ux, ux, uy * uy);
+  fluid_collide<T>(N, f, rho, drho, ux, uy, usq, pf);
+  compound_collide<T>(N, L, x, y, g, ux, uy, pg);
+}
+
+// The links of collide_node in place: where x + e_o is not fluid, pf[o] (and
+// pg[o]) becomes the value that arrives along opp(o), which for a wall it is
+// already; so only the open segments' links change anything. The whole
+// wavefront calls it; lanes that are not fluid pass lc = 0. Segment by
+// segment, so that a segment's parameters sit in scalar registers; held keeps
+// the last one's from call to call (of one phase). f, g: the state before the
+// collision (read only with PRESS).
+template <class T, bool PRESS, class FX>
+__device__ __forceinline__ void links_in_place(const NodeK<T> &N, CDesc &L, int x, int y,
+                                               uint32_t lc, const uint32_t *nbr,
+                                               const PhaseNow &ph, const T *f, const T *g, T *pf,
+                                               T *pg, T ux, T uy, T usq, SegHeld<T> &held,
+                                               FX &fx, bool count) {
+  const T q3 = pg[3], q4 = pg[4];  // (before the links along 1 and 2 replace them)
+#pragma unroll
+  for (int j = 1; j < 9; ++j) {
+    const int o = OPP[j];
+    const int code = (int)((nbr[(o - 1) >> 2] >> (8 * ((o - 1) & 3))) & 0xFFu);
+    const bool mine0 = ((lc >> (o - 1)) & 1u) && code >= GG_FIRST_SEGMENT &&
+                       ((ph.open >> (code - GG_FIRST_SEGMENT)) & 1u);
+    unsigned long long pend = __ballot(mine0);
+    while (pend) {
+      int s = __builtin_amdgcn_readlane(code, __ffsll(pend) - 1) - GG_FIRST_SEGMENT;
+      const bool mine = mine0 && code - GG_FIRST_SEGMENT == s;
+      asm("" : "+s"(s));  // (or the compiler would put the lane's equal value in its place)
+      if (s != held.s_) held.take(L, ph, s);
+      if (mine) {
+        T vf, vg = T(0);
+        open_link<T, PRESS>(N, held, j, x, y, PRESS ? f[j] : T(0), PRESS && j < 5 ? g[j] : T(0), pf[o], j < 5 ? pg[o] : T(0),
+                            j < 3 ? pg[j] : j == 3 ? q3 : j == 4 ? q4 : T(0), ux, uy, usq, vf, vg);
+        const T dm = vf - pf[o];
+        const T dc = (j < 5) ? vg - pg[o] : T(0);
+        pf[o] = vf;
+        if (j < 5) pg[o] = vg;
+        if (count) fx.add(s, dm, dc);
+      }
+      pend &= ~__ballot(mine);
+    }
+  }
+}
+
+// The same with the lattice's constants read from the descriptor as they are
+// used.
+template <class T>
+__device__ __forceinline__ void node_velocity(CDesc &L, const T *f, T &rho, T &drho, T &ux,
+                                              T &uy) {
+  node_velocity<T>(NodeK<T>(L), f, rho, drho, ux, uy);
+}
+template <class T>
+__device__ __forceinline__ void compound_collide(CDesc &L, int x, int y, const T *g, T ux, T uy,
+                                                 T *pg) {
+  compound_collide<T>(NodeK<T>(L), L, x, y, g, ux, uy, pg);
+}
+template <class T, bool PRESS = true, class FX = Flux>
+__device__ __forceinline__ void collide_node(CDesc &L, int x, int y, uint8_t lc, bool seg_tile,
+                                             const PhaseNow &ph, const T *f, const T *g, T *pf,
+                                             T *pg, T *in_f, T *in_g, FX &fx, bool count,
+                                             const uint32_t *nbr = nullptr) {
+  collide_node<T, PRESS, FX>(NodeK<T>(L), L, x, y, lc, seg_tile, ph, f, g, pf, pg, in_f, in_g, fx,
+                             count, nbr);
 }
 
 // Link rules of the compound alone (the compound lines of collide_node):
@@ -505,6 +670,58 @@ __device__ __forceinline__ void rescale_node(CDesc &L, int s, const PhaseNow &ph
       for (int i = 0; i < 5; ++i) g[i] = wg[i] * (cin - cs);
     }
     dc = (double)cin - (double)C;
+  }
+}
+
+// Post-collision populations qf, qg of node (x, y), pushed into the
+// neighbours' slots of the planes dst in natural order, or, toward a
+// non-fluid neighbour, jf, jg: the value that arrives here along the
+// opposite direction, into this node's own slot (the last step of every
+// pass). wrap (uniform): some neighbour of the wavefront's nodes lies across
+// a periodic edge.
+template <class S>
+__device__ __forceinline__ void push_node(CDesc &L, const Planes<typename Pop<S>::W> &dst, int x,
+                                          int y, bool wrap, uint8_t lc, const typename Pop<S>::T *qf,
+                                          const typename Pop<S>::T *qg,
+                                          const typename Pop<S>::T *jf,
+                                          const typename Pop<S>::T *jg) {
+  using P = Pop<S>;
+  const uint32_t node = (uint32_t)(L.node0 + y * L.pitch + x);
+  // slot i of neighbour x + e_i as nbp(i) gives it
+  auto push = [&](auto nbp) {
+    // (stores in pairs: one conversion for two values where FP16 is stored)
+    if (dst.pairs) {  // (uniform) f_i and g_i to x + e_i in one access
+      P::st_pair(dst.at(0, node), qf[0], qg[0]);
+#pragma unroll
+      for (int i = 1; i < 5; ++i) P::st_pair(nbp(i), qf[i], qg[i]);
+#pragma unroll
+      for (int i = 5; i < 9; i += 2) P::st2(nbp(i), nbp(i + 1), qf[i], qf[i + 1]);
+    } else {
+      P::st2(dst.at(0, node), dst.at(9, node), qf[0], qg[0]);
+#pragma unroll
+      for (int i = 1; i < 9; i += 2) P::st2(nbp(i), nbp(i + 1), qf[i], qf[i + 1]);
+#pragma unroll
+      for (int i = 1; i < 5; i += 2) P::st2(nbp(9 + i), nbp(10 + i), qg[i], qg[i + 1]);
+    }
+  };
+  if (!wrap) {
+    // the neighbours are node + e_x + e_y pitch, padding included:
+    // the row offset goes into the scalar base, the column offset into the
+    // store's immediate
+    const int pitch = L.pitch;
+    push([&](int k) { return dst.at_nb(k, node, EY[k > 8 ? k - 9 : k] * pitch, EX[k > 8 ? k - 9 : k]); });
+  } else {
+    const Neigh n(L, x, y);
+    push([&](int k) { return dst.at(k, n.idx[k > 8 ? k - 9 : k]); });
+  }
+  if (lc != 0) {
+    // x + e_i not fluid: the value arriving along opp(i) stays here
+#pragma unroll
+    for (int i = 1; i < 9; ++i)
+      if ((lc >> (i - 1)) & 1) P::st(dst.at(OPP[i], node), jf[OPP[i]]);
+#pragma unroll
+    for (int i = 1; i < 5; ++i)
+      if ((lc >> (i - 1)) & 1) P::st(dst.at(9 + OPP[i], node), jg[OPP[i]]);
   }
 }
 

@@ -16,6 +16,25 @@ struct SegHost {
   double s0 = 0.0, s1 = 1.0;  // halfway-wall tangential coordinates
 };
 
+// The form of the pipelined passes over a set of lattices: steps per pass,
+// rows per strip, and whether the segment strips run in a kernel of their own
+// on the side stream (fork) or in the one kernel with the others.
+struct PipePlan {
+  int steps = 4, rows = 16;
+  bool fork = false;
+  int width() const { return 64 - 2 * (steps - 1); }
+  int halo() const { return steps - 2; }  // build_pipe's
+};
+// A plan and its strips: those with segment links and the others, and the
+// fluid nodes each owns.
+struct PipeStrips {
+  PipePlan plan;
+  gg::Tile *d_main = nullptr, *d_seg = nullptr;
+  int n_main = 0, n_seg = 0;
+  int64_t main_fluid = 0, seg_fluid = 0;
+  bool none() const { return n_main + n_seg == 0; }
+};
+
 struct gg_lattice {
   gg_alloc alloc{};         // the caller's device allocator (has_alloc)
   bool has_alloc = false;
@@ -62,9 +81,8 @@ struct gg_lattice {
   // two-step pass: fuse = 2, 3, 4 advance pairs of steps in one pass over
   // memory (walking strips of 62 columns x strip_h rows, or row-parallel
   // tiles of strip_h rows with the boundary kernel apart or in one kernel);
-  // fuse = 5 runs runs of eight steps in four-step passes (58 x 6 tiles,
-  // the boundary kernel apart) and other runs as fuse = 3; fuse = 1 keeps
-  // to single steps
+  // fuse = 5 runs multiples of four steps in pipelined passes (launch_pipe)
+  // and other runs as fuse = 3; fuse = 1 keeps to single steps
   int fuse = 3, strip_h = 6;
   // population layout: paired (f_i, g_i side by side, i = 0..4) or
   // plane-major (gg_set_layout)
@@ -117,11 +135,10 @@ struct gg_lattice {
   hipGraphExec_t cde_exec[2] = {nullptr, nullptr};
   // fluid nodes owned by the tiles of the pass's two lists
   int64_t strips_fluid = 0, seg_strips_fluid = 0;
-  // the four-step pass's lists (fuse = 5 where the lattice allows it: no
-  // pressure segments, periodic axes of 4 nodes or more)
-  gg::Tile *d_strips4 = nullptr, *d_seg_strips4 = nullptr;
-  int n_strips4 = 0, n_seg_strips4 = 0;
-  int64_t strips4_fluid = 0, seg_strips4_fluid = 0;
+  // the pipelined passes' strips (fuse = 5 where the lattice allows it: no
+  // pressure segments, periodic axes of 4 nodes or more): [0] the passes, [1]
+  // those of four steps for what passes of eight leave over
+  PipeStrips pipe[2];
   bool tiles4 = false;  // the lists were built (pass4_ok held)
   // monitor: the FP64 reduction of gg_diagnostics launched after every
   // mon_every-th step (counted from mon_t0) into d_mon (8 totals, then the
@@ -130,7 +147,7 @@ struct gg_lattice {
   double *d_mon = nullptr;
   // profiling (gg_step_profile): plain launches with an event pair around
   // every launch of the dominant kernel; kind 0 pass, 1 even step, 2 odd
-  // step, 3 graph replay, 4 two-step pass beside the four-step pass
+  // step, 3 graph replay, 4 and 5 pipelined pass of 2 and 4 leftover steps
   bool prof = false;
   std::vector<hipEvent_t> prof_ev;
   std::vector<int8_t> prof_kind;

@@ -115,7 +115,8 @@ void gg_free_device(gg_lattice *L) {
   L->graph = nullptr;
   void *ptrs[] = {L->d_pop, L->d_pop_b, L->d_link, L->d_mask, L->d_region, L->d_R, L->d_t,
                   L->d_flux, L->d_acc, L->d_desc, L->d_tiles, L->d_aux_tiles, L->d_strips,
-                  L->d_seg_strips, L->d_strips4, L->d_seg_strips4, L->d_partial, L->d_ufield,
+                  L->d_seg_strips, L->pipe[0].d_main, L->pipe[0].d_seg, L->pipe[1].d_main,
+                  L->pipe[1].d_seg, L->d_partial, L->d_ufield,
                   L->d_cde_tiles, L->d_cde_tiles4, L->d_press, L->d_wall, L->d_wall_links,
                   L->d_wall_save,
                   L->d_mon};
@@ -312,14 +313,219 @@ static void build_strips(const gg_lattice *L, int h, int inst, bool split, std::
   }
 }
 
+// Strips of the pipelined passes (launch_pipe): `width` owned columns x at
+// most h rows, band by band from the first fluid row, laid from the first
+// column of each run of fluid columns of the band and cut to the rows that
+// hold fluid. Rows with a link to a boundary segment among the nodes whose
+// state the strip completes (within `halo` nodes of the row) go to the
+// second list, in pieces of a quarter of their run and at most 8 rows, the
+// rows between them to the first: the boundary rules make a row slower and a
+// strip takes its rows one after another, so a long segment strip would
+// outlast the others (2048 x 1024 gradient generator, FP32: 6.4 us a step
+// with 4-row segment strips, 5.9 with 1-row ones). Flags: rows << 8 | bits.
+static void build_pipe(const gg_lattice *L, int h, int inst, int width, int halo,
+                       std::vector<Tile> &main, std::vector<Tile> &seg) {
+  const int nx = L->nx, ny = L->ny;
+  bool any_segment = false;
+  for (bool b : L->seg_present) any_segment = any_segment || b;
+  // columns of the segment-touching nodes of each row
+  std::vector<std::vector<int>> touch((size_t)ny);
+  std::vector<std::pair<int, int>> span((size_t)ny, {nx, -1});  // fluid columns of each row
+  for (int y = 0; y < ny; ++y) {
+    const uint8_t *lk = &L->link[L->nid(0, y)];
+    int a = 0, b = nx - 1;
+    while (a < nx && lk[a] == NOT_FLUID) ++a;
+    while (b >= a && lk[b] == NOT_FLUID) --b;
+    span[y] = {a, b};
+    if (a > b || !any_segment) continue;
+    const uint8_t *ts = &L->touches_seg[(size_t)y * nx];
+    for (int x = a; x <= b; ++x)
+      if (ts[x] && lk[x] != NOT_FLUID) touch[y].push_back(x);
+  }
+  // is a segment-touching node within `halo` nodes of columns x0.. of row y
+  auto near_seg = [&](int x0, int y) {
+    for (int dy = -halo; dy <= halo; ++dy) {
+      int yy = y + dy;
+      if (yy < 0 || yy >= ny) {
+        if (!L->p.periodic_y) continue;
+        yy = (yy + ny) % ny;
+      }
+      for (int x : touch[yy])
+        for (int wrap = L->p.periodic_x ? -1 : 0; wrap <= (L->p.periodic_x ? 1 : 0); ++wrap)
+          if (x + wrap * nx >= x0 - halo && x + wrap * nx <= x0 + width - 1 + halo) return true;
+    }
+    return false;
+  };
+  // has any node within halo + 1 nodes of the columns x0.. and rows y0..y1 - 1
+  // a non-fluid neighbour (or is it none)
+  auto links_in = [&](int x0, int y0, int y1) {
+    const int m = halo + 1, xa = x0 - m, xb = x0 + width + m;  // [xa, xb)
+    if (!L->p.periodic_x && (xa < 0 || xb > nx)) return true;
+    for (int yr = y0 - m; yr < y1 + m; ++yr) {
+      int y = yr;
+      if (y < 0 || y >= ny) {
+        if (!L->p.periodic_y) return true;
+        y = (y + ny) % ny;
+      }
+      const uint8_t *lk = &L->link[L->nid(0, y)];
+      const int a = std::max(xa, 0), b = std::min(xb, nx);
+      uint8_t any = 0;
+      for (int x = a; x < b; ++x) any |= lk[x];
+      for (int x = xa; x < 0; ++x) any |= lk[(x + nx) % nx];
+      for (int x = nx; x < xb; ++x) any |= lk[x % nx];
+      if (any) return true;
+    }
+    return false;
+  };
+  int y_first = 0;
+  while (y_first < ny && span[y_first].first > span[y_first].second) ++y_first;
+  std::vector<uint8_t> colany((size_t)nx);
+  for (int y0 = y_first; y0 < ny; y0 += h) {
+    const int y1 = std::min(y0 + h, ny);
+    std::fill(colany.begin(), colany.end(), 0);
+    for (int y = y0; y < y1; ++y) {
+      const uint8_t *lk = &L->link[L->nid(0, y)];
+      for (int x = span[y].first; x <= span[y].second; ++x) colany[x] |= lk[x] != NOT_FLUID;
+    }
+    std::vector<std::pair<int, int>> runs;  // runs less than a strip apart are merged
+    for (int x = 0; x < nx;) {
+      if (!colany[x]) {
+        ++x;
+        continue;
+      }
+      int e = x;
+      while (e < nx && colany[e]) ++e;
+      if (!runs.empty() && x - runs.back().second < width)
+        runs.back().second = e;
+      else
+        runs.push_back({x, e});
+      x = e;
+    }
+    for (const auto &run : runs)
+      for (int x0 = run.first; x0 < run.second; x0 += width) {
+        const int x1 = std::min(x0 + width, nx);
+        auto any = [&](int y) {
+          const uint8_t *lk = &L->link[L->nid(0, y)];
+          for (int x = x0; x < x1; ++x)
+            if (lk[x] != NOT_FLUID) return true;
+          return false;
+        };
+        int ya = y0, yb = y1;
+        while (ya < yb && !any(ya)) ++ya;
+        while (yb > ya && !any(yb - 1)) --yb;
+        for (int y = ya; y < yb;) {
+          const bool sg = near_seg(x0, y);
+          int e = y + 1;
+          while (e < yb && near_seg(x0, e) == sg) ++e;
+          const int piece = sg ? std::max(1, std::min(8, (e - y) / 4)) : e - y;
+          const int flags = sg ? TILE_TOUCHES_SEGMENT | TILE_HAS_LINKS
+                               : (links_in(x0, y, e) ? TILE_HAS_LINKS : 0);
+          for (; y < e; y += piece)
+            (sg ? seg : main)
+                .push_back(Tile{inst, x0, y, (std::min(piece, e - y) << 8) | flags});
+          y = e;
+        }
+      }
+  }
+}
+
+// Rows of strips of `width` columns that cover the fluid (runs of fluid
+// columns less than a strip apart taken as one, as build_pipe does).
+static int64_t pipe_strip_rows(const gg_lattice *L, int width) {
+  int64_t n = 0;
+  for (int y = 0; y < L->ny; ++y) {
+    const uint8_t *lk = &L->link[L->nid(0, y)];
+    for (int x = 0; x < L->nx;) {
+      while (x < L->nx && lk[x] == NOT_FLUID) ++x;
+      if (x == L->nx) break;
+      const int a = x;
+      int last = x;
+      for (; x < L->nx && x - last <= width; ++x)
+        if (lk[x] != NOT_FLUID) last = x;
+      x = last + 1;
+      n += (last + 1 - a + width - 1) / width;
+    }
+  }
+  return n;
+}
+
+// Rows per strip: the pass takes as many rounds of work-groups as `slots` of
+// them at once allow, each rows + 3 (steps - 1) iterations long and a few
+// more to start, and an iteration takes longer the more work-groups share a
+// CU (measured: about 0.45 + 0.17 n us with n of them). In the Infinity Cache
+// (cached) the rounds are even; beyond it the work-groups drift apart and
+// start one by one, and the tail costs the better part of a round. Measured:
+// 2048 x 1024 gradient generator FP32 5.9-6.0 us a step with 10..14 rows, 6.3
+// with 16, FP64 8.5 with 14 (one round) and 10.4 with 12 (two); 6144 x 3072
+// FP32 29.3 with 48 rows (2.3 rounds), 38.5 with 128 (0.9); 8192 x 4096
+// all-fluid 152 with 96 and 128, 164 with 48.
+static int pipe_pick_rows(int64_t strip_rows, int steps, int slots, int cus, bool cached) {
+  int best = 16;
+  double best_cost = 0.0;
+  for (int rows : {8, 10, 12, 14, 16, 20, 24, 32, 48, 64, 96, 128}) {
+    const double strips = std::max(1.0, (double)strip_rows / rows);
+    double rounds = strips * 1.03 / slots;
+    rounds = !cached ? rounds + 0.8 : rounds > 4.0 ? rounds + 0.5 : std::ceil(rounds);
+    const double share = std::max(1.0, std::min(strips, (double)slots) / cus);
+    const double cost = rounds * (rows + 3 * (steps - 1) + 4) *
+                        (cached ? 0.45 + 0.17 * share : 1.0);
+    if (best_cost == 0.0 || cost < best_cost) {
+      best = rows;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// Steps per pass: 8 for FP32 once the two plane sets outgrow the Infinity
+// Cache (256 MB; at 114 bytes a node, from about 2M nodes): the pass is then
+// bound by its memory pattern and half the trips pay for the wider halo
+// (8192 x 4096 all-fluid 145 us a step with 8, 234 with 4; 8192 x 512 25.2
+// and 32.3). Inside the cache the longer pipeline fill costs more than the
+// trips save (the 2048 x 1024 gradient generator keeps 4). FP16 is bound by
+// its arithmetic with 4 already (143-150 us a step with 8, 145 with 4), and
+// FP64 has LDS for too few work-groups of 8 (or 6: 551 against 416).
+constexpr int64_t PIPE8_NODES = 2000000;
+static PipePlan pipe_plan(const gg_lattice *const *lats, int n, int max_steps) {
+  PipePlan p;
+  int64_t fluid = 0;
+  bool wrap8 = true, segments = false;
+  for (int k = 0; k < n; ++k) {
+    fluid += lats[k]->n_fluid;
+    wrap8 = wrap8 && (!lats[k]->p.periodic_x || lats[k]->nx >= 8) &&
+            (!lats[k]->p.periodic_y || lats[k]->ny >= 8);
+    for (bool b : lats[k]->seg_present) segments = segments || b;
+  }
+  const gg_storage st = lats[0]->storage;
+  if (max_steps >= 8 && st == GG_F32 && wrap8 && fluid >= PIPE8_NODES) p.steps = 8;
+  const bool cached = fluid * 2 * NPOP * (int64_t)lats[0]->esize <= (int64_t)256 << 20;
+  int64_t strip_rows = 0;
+  for (int k = 0; k < n; ++k) strip_rows += pipe_strip_rows(lats[k], p.width());
+  // segment strips in the one kernel while all work-groups fit at once or
+  // nearly: its register budget then costs nothing, and a second kernel's
+  // fork and join would (about 8 us a pass)
+  int cus = 256;
+  int slots = pipe_slots(st, lats[0]->pairs, p.steps, segments, &cus);
+  p.rows = pipe_pick_rows(strip_rows, p.steps, slots, cus, cached);
+  if (segments && strip_rows / p.rows > 3 * slots / 2) {
+    p.fork = true;
+    slots = pipe_slots(st, lats[0]->pairs, p.steps, false, &cus);
+    p.rows = pipe_pick_rows(strip_rows, p.steps, slots, cus, cached);
+  }
+  return p;
+}
+
 // Fluid nodes owned by a list of pass tiles (width columns x the rows in
 // the flags of each).
-static int64_t owned_fluid(const gg_lattice *L, const std::vector<Tile> &list, int width = 62) {
+static int64_t owned_fluid(const gg_lattice *L, const std::vector<Tile> &list, int width = 62,
+                           size_t first = 0) {
   int64_t n = 0;
-  for (const Tile &t : list)
+  for (size_t k = first; k < list.size(); ++k) {
+    const Tile &t = list[k];
     for (int y = t.y0; y < std::min(t.y0 + (t.flags >> 8), L->ny); ++y)
       for (int x = t.x0; x < std::min(t.x0 + width, L->nx); ++x)
         n += L->link[L->nid(x, y)] != NOT_FLUID;
+  }
   return n;
 }
 
@@ -331,6 +537,76 @@ static bool has_pressure(const gg_lattice *L);
 static bool pass4_ok(const gg_lattice *L) {
   return L->fuse == 5 && !has_pressure(L) && L->wall_scheme == 0 &&
          (!L->p.periodic_x || L->nx >= 4) && (!L->p.periodic_y || L->ny >= 4);
+}
+
+// The strips of the pipelined passes over the n lattices (n = 0: none) into
+// lists[0..1], in device memory of `owner`'s allocator (null: hipMalloc).
+static gg_status pipe_strips(const gg_lattice *const *lats, int n, const gg_lattice *owner,
+                             PipeStrips *lists) {
+  auto alloc = [&](void **q, size_t bytes) { return owner ? dev_alloc(owner, q, bytes) : hipMalloc(q, bytes); };
+  for (int i = 0; i < 2; ++i) {
+    PipeStrips &p = lists[i];
+    for (Tile *d : {p.d_main, p.d_seg})
+      if (d) (void)(owner ? dev_free(owner, d) : hipFree(d));
+    p = PipeStrips();
+  }
+  for (int i = 0; i < 2 && n > 0; ++i) {
+    if (i == 1 && lists[0].plan.steps <= 4) break;
+    PipeStrips &p = lists[i];
+    p.plan = pipe_plan(lats, n, i == 0 ? 8 : 4);
+    std::vector<Tile> main, seg;
+    for (int k = 0; k < n; ++k) {
+      const size_t m0 = main.size(), s0 = seg.size();
+      build_pipe(lats[k], p.plan.rows, k, p.plan.width(), p.plan.halo(), main, seg);
+      p.main_fluid += owned_fluid(lats[k], main, p.plan.width(), m0);
+      p.seg_fluid += owned_fluid(lats[k], seg, p.plan.width(), s0);
+    }
+    auto put = [&](const std::vector<Tile> &list, Tile *&d, int &count) -> gg_status {
+      if (list.empty()) return GG_OK;
+      GG_HIP(alloc((void **)&d, list.size() * sizeof(Tile)));
+      GG_HIP(hipMemcpy(d, list.data(), list.size() * sizeof(Tile), hipMemcpyHostToDevice));
+      count = (int)list.size();
+      return GG_OK;
+    };
+    gg_status st = put(main, p.d_main, p.n_main);
+    if (st == GG_OK) st = put(seg, p.d_seg, p.n_seg);
+    if (st != GG_OK) return st;
+  }
+  return GG_OK;
+}
+
+// One pipelined pass of `steps` steps over the strips p: the segment strips in
+// the one kernel with the others or, forked and joined, beside them.
+static hipError_t launch_strips(gg_storage storage, bool pairs, const LatDesc *d,
+                                const PipeStrips &p, int dir, int dt, int steps, hipStream_t st,
+                                hipStream_t side, hipEvent_t ev_fork, hipEvent_t ev_join) {
+  auto run = [&](const Tile *sl, int ns, const Tile *ml, int nm, hipStream_t q) {
+    return launch_pipe(storage, pairs, p.plan.steps, d, sl, ns, ml, nm, dir, dt, steps, q);
+  };
+  if (!(p.plan.fork && p.n_seg > 0 && p.n_main > 0))
+    return run(p.d_seg, p.n_seg, p.d_main, p.n_main, st);
+  hipError_t e = hipEventRecord(ev_fork, st);
+  if (e == hipSuccess) e = hipStreamWaitEvent(side, ev_fork, 0);
+  if (e == hipSuccess) e = run(p.d_seg, p.n_seg, nullptr, 0, side);
+  if (e == hipSuccess) e = hipEventRecord(ev_join, side);
+  if (e == hipSuccess) e = run(nullptr, 0, p.d_main, p.n_main, st);
+  if (e == hipSuccess) e = hipStreamWaitEvent(st, ev_join, 0);
+  return e;
+}
+
+// n steps (a multiple of four, from an even step) in pairs of pipelined passes
+// (which end in the first plane set), the last ones of fewer steps:
+// launch(strips, dir, dt, steps) launches one.
+template <class F>
+static hipError_t launch_pipes(const PipeStrips *lists, int64_t n, F &&launch) {
+  hipError_t e = hipSuccess;
+  const PipeStrips &rest = lists[1].none() ? lists[0] : lists[1];
+  int64_t done = 0;
+  for (int steps : {lists[0].plan.steps, 4, 2})
+    for (; n - done >= 2 * steps && e == hipSuccess; done += 2 * steps)
+      for (int k = 0; k < 2 && e == hipSuccess; ++k)
+        e = launch(steps > 4 ? lists[0] : rest, k, (int)done + k * steps, steps);
+  return e;
 }
 
 gg_status gg_rebuild_tiles(gg_lattice *L) {
@@ -363,37 +639,12 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
     GG_HIP(dev_alloc(L, (void **)&L->d_seg_strips, ss.size() * sizeof(Tile)));
     GG_HIP(hipMemcpy(L->d_seg_strips, ss.data(), ss.size() * sizeof(Tile), hipMemcpyHostToDevice));
   }
-  // the four-step pass's lists (6-row tiles, 2-row boundary tiles)
-  if (L->d_strips4) (void)dev_free(L, L->d_strips4);
-  if (L->d_seg_strips4) (void)dev_free(L, L->d_seg_strips4);
-  L->d_strips4 = L->d_seg_strips4 = nullptr;
-  L->n_strips4 = L->n_seg_strips4 = 0;
-  L->strips4_fluid = L->seg_strips4_fluid = 0;
+  // the pipelined passes' strips
   L->tiles4 = pass4_ok(L);
-  if (L->tiles4) {
-    std::vector<Tile> m4, s4;
-    build_strips(L, 6, 0, true, m4, s4, 2, 58);
-    // in eight vertical stripes, each walked band by band: an XCD takes a
-    // contiguous run of the list, and the tiles above and below a tile
-    // (which share its three halo rows, half of what it loads) then run
-    // soon after it on the same L2; a whole band of the lattice with its
-    // halo rows need not fit in one XCD's L2
-    std::stable_sort(m4.begin(), m4.end(), [&](const Tile &a, const Tile &b) {
-      const int sa = (int)((int64_t)a.x0 * 8 / L->nx), sb = (int)((int64_t)b.x0 * 8 / L->nx);
-      return sa != sb ? sa < sb : (a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0);
-    });
-    L->n_strips4 = (int)m4.size();
-    L->n_seg_strips4 = (int)s4.size();
-    L->strips4_fluid = owned_fluid(L, m4, 58);
-    L->seg_strips4_fluid = owned_fluid(L, s4, 58);
-    if (!m4.empty()) {
-      GG_HIP(dev_alloc(L, (void **)&L->d_strips4, m4.size() * sizeof(Tile)));
-      GG_HIP(hipMemcpy(L->d_strips4, m4.data(), m4.size() * sizeof(Tile), hipMemcpyHostToDevice));
-    }
-    if (!s4.empty()) {
-      GG_HIP(dev_alloc(L, (void **)&L->d_seg_strips4, s4.size() * sizeof(Tile)));
-      GG_HIP(hipMemcpy(L->d_seg_strips4, s4.data(), s4.size() * sizeof(Tile), hipMemcpyHostToDevice));
-    }
+  {
+    const gg_lattice *self[1] = {L};
+    const gg_status st = pipe_strips(self, L->tiles4 ? 1 : 0, L, L->pipe);
+    if (st != GG_OK) return st;
   }
   if (L->graph_exec) (void)hipGraphExecDestroy(L->graph_exec);
   if (L->graph) (void)hipGraphDestroy(L->graph);
@@ -1005,41 +1256,20 @@ static hipError_t launch_pass(gg_lattice *L, int dir, int dt, hipStream_t st) {
   return e;
 }
 
-// One four-step pass: the boundary tiles on the side stream as in
-// launch_pass.
-static hipError_t launch_pass4(gg_lattice *L, int dir, int dt, hipStream_t st) {
-  hipError_t e = hipSuccess;
-  const bool fork = L->n_seg_strips4 > 0 && L->n_strips4 > 0;
-  if (fork) {
-    e = hipEventRecord(L->ev_fork, st);
-    if (e == hipSuccess) e = hipStreamWaitEvent(L->side, L->ev_fork, 0);
-    if (e == hipSuccess)
-      e = launch_tile4(L->storage, L->pairs, true, L->d_desc, L->d_seg_strips4, L->n_seg_strips4,
-                       dir, dt, L->side);
-    if (e == hipSuccess) e = hipEventRecord(L->ev_join, L->side);
-  } else if (L->n_seg_strips4 > 0) {
-    e = launch_tile4(L->storage, L->pairs, true, L->d_desc, L->d_seg_strips4, L->n_seg_strips4, dir,
-                     dt, st);
-  }
-  long pidx = -1;
-  if (e == hipSuccess) e = prof_begin(L, st, pidx);
-  if (e == hipSuccess)
-    e = launch_tile4(L->storage, L->pairs, false, L->d_desc, L->d_strips4, L->n_strips4, dir, dt, st);
-  if (e == hipSuccess) e = prof_end(L, st, pidx, 0);
-  if (fork && e == hipSuccess) e = hipStreamWaitEvent(st, L->ev_join, 0);
-  return e;
-}
-
 static hipError_t launch_steps(gg_lattice *L, int64_t t0, int64_t n, hipStream_t st) {
   hipError_t e = hipSuccess;
   if (L->tiles4 && pass4_ok(L) && !(t0 & 1) && n % 4 == 0) {
-    // four-step passes in pairs (ending in the first plane set), then the
-    // last four steps of a run of 8k + 4 in two two-step passes
-    const int64_t p4 = n / 8 * 2;
-    for (int64_t k = 0; k < p4 && e == hipSuccess; ++k)
-      e = launch_pass4(L, (int)(k & 1), (int)(4 * k), st);
-    for (int64_t k = 0; k < (n % 8) / 2 && e == hipSuccess; ++k)
-      e = launch_pass(L, (int)(k & 1), (int)(4 * p4 + 2 * k), st);
+    e = launch_pipes(L->pipe, n, [&](const PipeStrips &p, int dir, int dt, int steps) {
+      // (with the segment strips beside them, the pair of events spans both)
+      long pidx = -1;
+      hipError_t r = prof_begin(L, st, pidx);
+      if (r == hipSuccess)
+        r = launch_strips(L->storage, L->pairs, L->d_desc, p, dir, dt, steps, st, L->side,
+                          L->ev_fork, L->ev_join);
+      if (r == hipSuccess)
+        r = prof_end(L, st, pidx, steps == L->pipe[0].plan.steps ? 0 : steps == 4 ? 5 : 4);
+      return r;
+    });
   } else if (pass_ok(L) && !(t0 & 1) && n % 4 == 0) {
     // with pressure segments the pass rescales the boundary nodes between
     // its two steps; the state it leaves is rescaled by the kernel after
@@ -1238,13 +1468,13 @@ gg_status gg_step_profile(gg_lattice *L, int64_t n, gg_profile *out) {
     if (kind == 0) {
       out->n_pass += 1;
       out->ms_pass += x;
-    } else if (kind == 4) {
-      out->n_pass2 += 1;
+    } else if (kind == 4 || kind == 5) {  // (a leftover pass of 2, of 4 steps)
+      out->n_pass2 += kind == 4 ? 1 : 2;
       out->ms_pass2 += x;
     } else if (kind == 3) {
       out->n_graph += 1;
       out->ms_graph += x;
-      if (L->tiles4 && pass4_ok(L)) out->graph_passes += L->graph_chunk / 4;
+      if (L->tiles4 && pass4_ok(L)) out->graph_passes += L->graph_chunk / L->pipe[0].plan.steps;
       else if (pass_ok(L)) out->graph_passes += L->graph_chunk / 2;
       else out->graph_singles += L->graph_chunk;
     } else {
@@ -1262,13 +1492,14 @@ gg_status gg_step_profile(gg_lattice *L, int64_t n, gg_profile *out) {
   out->pass_side_fluid = L->fuse == 4 ? 0 : L->seg_strips_fluid;
   out->pass_tiles = L->n_strips;
   out->pass_side_tiles = L->fuse == 4 ? 0 : L->n_seg_strips;
-  if (L->tiles4 && pass4_ok(L)) {  // the four-step pass's interior kernel
-    out->rows = 6;
-    out->steps_per_pass = 4;
-    out->pass_fluid = L->strips4_fluid;
-    out->pass_side_fluid = L->seg_strips4_fluid;
-    out->pass_tiles = L->n_strips4;
-    out->pass_side_tiles = L->n_seg_strips4;
+  if (L->tiles4 && pass4_ok(L)) {  // the pipelined pass
+    const PipeStrips &p = L->pipe[0];
+    out->rows = p.plan.rows;
+    out->steps_per_pass = p.plan.steps;
+    out->pass_fluid = p.main_fluid + (p.plan.fork ? 0 : p.seg_fluid);
+    out->pass_side_fluid = p.plan.fork ? p.seg_fluid : 0;
+    out->pass_tiles = p.n_main + (p.plan.fork ? 0 : (p.n_seg + 7) / 8 * 8);
+    out->pass_side_tiles = p.plan.fork ? p.n_seg : 0;
   }
   return st;
 }
@@ -1460,6 +1691,14 @@ gg_status gg_load(gg_lattice *L, const void *buf, size_t nbytes) {
   return GG_OK;
 }
 
+// Graph chunks are even (a multiple of 4 with the two-step pass, of 8 or 16
+// with pipelined passes of 4 or 8 steps): replays keep the parity and run
+// whole passes.
+static int chunk_quantum(const gg_lattice *L) {
+  if (L->fuse == 5) return L->tiles4 ? 2 * L->pipe[0].plan.steps : 8;
+  return L->fuse >= 2 ? 4 : 2;
+}
+
 gg_status gg_set_launch(gg_lattice *L, int32_t tile_x, int32_t tile_y, int32_t graph_chunk) {
   if (!L) return fail(GG_ERR_ARG, "lattice is NULL");
   const int bs = tile_x * tile_y;
@@ -1470,12 +1709,12 @@ gg_status gg_set_launch(gg_lattice *L, int32_t tile_x, int32_t tile_y, int32_t g
   GG_HIP(hipStreamSynchronize(L->stream));
   L->tile_x = tile_x;
   L->tile_y = tile_y;
-  // even (a multiple of 4 with the two-step pass, of 8 with the four-step
-  // pass): replays keep the parity and run whole passes
-  const int q = L->fuse == 5 ? 8 : L->fuse >= 2 ? 4 : 2;
-  L->graph_chunk = (graph_chunk + q - 1) / q * q;
   gg_drop_cde_graphs(L);
-  return gg_rebuild_tiles(L);
+  const gg_status st = gg_rebuild_tiles(L);
+  if (st != GG_OK) return st;
+  const int q = chunk_quantum(L);
+  L->graph_chunk = (graph_chunk + q - 1) / q * q;
+  return GG_OK;
 }
 
 gg_status gg_set_two_step(gg_lattice *L, int32_t fuse, int32_t strip_h) {
@@ -1505,12 +1744,13 @@ gg_status gg_set_two_step(gg_lattice *L, int32_t fuse, int32_t strip_h) {
   }
   L->fuse = fuse;
   if (fuse >= 2) L->strip_h = strip_h;
-  const int q = fuse == 5 ? 8 : fuse >= 2 ? 4 : 2;
-  L->graph_chunk = (L->graph_chunk + q - 1) / q * q;
   gg_drop_cde_graphs(L);
   gg_status st = gg_upload_desc(L);
+  if (st == GG_OK) st = gg_rebuild_tiles(L);
   if (st != GG_OK) return st;
-  return gg_rebuild_tiles(L);
+  const int q = chunk_quantum(L);
+  L->graph_chunk = (L->graph_chunk + q - 1) / q * q;
+  return GG_OK;
 }
 
 gg_status gg_info(const gg_lattice *L, int64_t *n_fluid, int64_t *n_tiles, int64_t *t) {
@@ -1781,13 +2021,11 @@ struct gg_batch {
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   // two-step pass over all members (fuse 3 or 4, tiles of `rows` rows);
-  // fuse 5: four-step passes over the members' 58 x 6 tiles (the lists
-  // with 4), two-step passes as fuse 3 for the last four steps of 8k + 4
+  // fuse 5: pipelined passes over the members' strips
   int fuse = 1, rows = 6;
   Tile *d_strips = nullptr, *d_seg_strips = nullptr;
   int n_strips = 0, n_seg_strips = 0;
-  Tile *d_strips4 = nullptr, *d_seg_strips4 = nullptr;
-  int n_strips4 = 0, n_seg_strips4 = 0;
+  PipeStrips pipe[2];
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
 };
@@ -1800,8 +2038,9 @@ static void batch_free(gg_batch *B) {
     if (B->d_tiles[g]) (void)hipFree(B->d_tiles[g]);
   if (B->d_strips) (void)hipFree(B->d_strips);
   if (B->d_seg_strips) (void)hipFree(B->d_seg_strips);
-  if (B->d_strips4) (void)hipFree(B->d_strips4);
-  if (B->d_seg_strips4) (void)hipFree(B->d_seg_strips4);
+  for (const PipeStrips &p : B->pipe)
+    for (Tile *d : {p.d_main, p.d_seg})
+      if (d) (void)hipFree(d);
   if (B->cap_stream) (void)hipStreamDestroy(B->cap_stream);
   if (B->side) (void)hipStreamDestroy(B->side);
   if (B->ev_fork) (void)hipEventDestroy(B->ev_fork);
@@ -1832,41 +2071,39 @@ static gg_status batch_check_members(const gg_batch *B) {
 static hipError_t batch_launch(gg_batch *B, int64_t s0, int64_t n, hipStream_t st) {
   hipError_t e = hipSuccess;
   if (batch_passes(B, s0, n)) {
-    // one pass over all members: the boundary tiles' kernel on the side
-    // stream (forked and joined) when both lists hold tiles
-    auto pass = [&](bool four, int dir, int dt) -> hipError_t {
-      const Tile *main = four ? B->d_strips4 : B->d_strips;
-      const Tile *segl = four ? B->d_seg_strips4 : B->d_seg_strips;
-      const int nm = four ? B->n_strips4 : B->n_strips;
-      const int ns = four ? B->n_seg_strips4 : B->n_seg_strips;
-      // (the boundary list holds 2-row tiles; fuse 4's one list, run with
-      // the boundary rules, holds tiles of `rows` rows)
-      auto run = [&](bool seg, bool seg_list, const Tile *list, int nl, hipStream_t s) {
-        return four ? launch_tile4(B->storage, B->pairs, seg, B->d_descs, list, nl, dir, dt, s)
-                    : launch_tile2(B->storage, B->pairs, seg, seg_list ? 2 : B->rows, B->d_descs, list,
-                                   nl, dir, dt, s);
-      };
-      if (B->fuse == 4) return run(true, false, main, nm, st);
-      const bool fork = ns > 0 && nm > 0;
-      hipError_t r = hipSuccess;
-      if (fork) {
-        r = hipEventRecord(B->ev_fork, st);
-        if (r == hipSuccess) r = hipStreamWaitEvent(B->side, B->ev_fork, 0);
-        if (r == hipSuccess) r = run(true, true, segl, ns, B->side);
-        if (r == hipSuccess) r = hipEventRecord(B->ev_join, B->side);
-      } else if (ns > 0) {
-        r = run(true, true, segl, ns, st);
-      }
-      if (r == hipSuccess) r = run(false, false, main, nm, st);
-      if (fork && r == hipSuccess) r = hipStreamWaitEvent(st, B->ev_join, 0);
+    // one pass over all members: with boundary tiles apart, their kernel on
+    // the side stream (forked and joined)
+    auto apart = [&](bool fork, auto &&seg, auto &&main) -> hipError_t {
+      if (!fork) return main(st);
+      hipError_t r = hipEventRecord(B->ev_fork, st);
+      if (r == hipSuccess) r = hipStreamWaitEvent(B->side, B->ev_fork, 0);
+      if (r == hipSuccess) r = seg(B->side);
+      if (r == hipSuccess) r = hipEventRecord(B->ev_join, B->side);
+      if (r == hipSuccess) r = main(st);
+      if (r == hipSuccess) r = hipStreamWaitEvent(st, B->ev_join, 0);
       return r;
     };
-    // fuse 5: four-step passes in pairs, then the last four steps of a
-    // run of 8k + 4 in two two-step passes
-    const int64_t p4 = B->fuse == 5 ? n / 8 * 2 : 0;
-    for (int64_t k = 0; k < p4 && e == hipSuccess; ++k) e = pass(true, (int)(k & 1), (int)(4 * k));
-    for (int64_t k = 0; k < (n - 4 * p4) / 2 && e == hipSuccess; ++k)
-      e = pass(false, (int)(k & 1), (int)(4 * p4 + 2 * k));
+    // (the boundary list holds 2-row tiles; fuse 4's one list, run with the
+    // boundary rules, holds tiles of `rows` rows)
+    auto pass = [&](int dir, int dt) -> hipError_t {
+      auto run = [&](bool seg, int rows, const Tile *list, int nl, hipStream_t q) {
+        return launch_tile2(B->storage, B->pairs, seg, rows, B->d_descs, list, nl, dir, dt, q);
+      };
+      if (B->fuse == 4) return run(true, B->rows, B->d_strips, B->n_strips, st);
+      if (B->n_strips == 0) return run(true, 2, B->d_seg_strips, B->n_seg_strips, st);
+      return apart(
+          B->n_seg_strips > 0,
+          [&](hipStream_t q) { return run(true, 2, B->d_seg_strips, B->n_seg_strips, q); },
+          [&](hipStream_t q) { return run(false, B->rows, B->d_strips, B->n_strips, q); });
+    };
+    if (B->fuse == 5) {
+      e = launch_pipes(B->pipe, n, [&](const PipeStrips &p, int dir, int dt, int steps) {
+        return launch_strips(B->storage, B->pairs, B->d_descs, p, dir, dt, steps, st, B->side,
+                             B->ev_fork, B->ev_join);
+      });
+    } else {
+      for (int64_t k = 0; k < n / 2 && e == hipSuccess; ++k) e = pass((int)(k & 1), (int)(2 * k));
+    }
   } else {
     const int block = B->tile_x * B->tile_y;
     const int txs = ilog2(B->tile_x);
@@ -2177,28 +2414,16 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
   if (B->d_seg_strips) (void)hipFree(B->d_seg_strips);
   B->d_strips = B->d_seg_strips = nullptr;
   B->n_strips = B->n_seg_strips = 0;
-  if (B->d_strips4) (void)hipFree(B->d_strips4);
-  if (B->d_seg_strips4) (void)hipFree(B->d_seg_strips4);
-  B->d_strips4 = B->d_seg_strips4 = nullptr;
-  B->n_strips4 = B->n_seg_strips4 = 0;
+  {
+    const gg_status st = pipe_strips(B->lats.data(), fuse == 5 ? (int)B->lats.size() : 0, nullptr, B->pipe);
+    if (st != GG_OK) return st;
+  }
   B->fuse = fuse;
   B->rows = rows;
   if (fuse == 1) return GG_OK;
-  std::vector<Tile> sv, ss, sv4, ss4;
-  for (size_t k = 0; k < B->lats.size(); ++k) {
+  std::vector<Tile> sv, ss;
+  for (size_t k = 0; k < B->lats.size() && fuse != 5; ++k)
     build_strips(B->lats[k], rows, (int)k, fuse != 4, sv, ss);
-    if (fuse == 5) build_strips(B->lats[k], 6, (int)k, true, sv4, ss4, 2, 58);
-  }
-  B->n_strips4 = (int)sv4.size();
-  B->n_seg_strips4 = (int)ss4.size();
-  if (!sv4.empty()) {
-    GG_HIP(hipMalloc(&B->d_strips4, sv4.size() * sizeof(Tile)));
-    GG_HIP(hipMemcpy(B->d_strips4, sv4.data(), sv4.size() * sizeof(Tile), hipMemcpyHostToDevice));
-  }
-  if (!ss4.empty()) {
-    GG_HIP(hipMalloc(&B->d_seg_strips4, ss4.size() * sizeof(Tile)));
-    GG_HIP(hipMemcpy(B->d_seg_strips4, ss4.data(), ss4.size() * sizeof(Tile), hipMemcpyHostToDevice));
-  }
   B->n_strips = (int)sv.size();
   B->n_seg_strips = (int)ss.size();
   if (!sv.empty()) {
@@ -2214,8 +2439,8 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
     GG_HIP(hipEventCreateWithFlags(&B->ev_fork, hipEventDisableTiming));
     GG_HIP(hipEventCreateWithFlags(&B->ev_join, hipEventDisableTiming));
   }
-  // replays run whole passes: a multiple of 4 steps, of 8 with fuse 5
-  const int q = fuse == 5 ? 8 : 4;
+  // replays run whole passes: a multiple of 4 steps, of 8 or 16 with fuse 5
+  const int q = fuse == 5 ? 2 * B->pipe[0].plan.steps : 4;
   B->chunk = (B->chunk + q - 1) / q * q;
   return GG_OK;
 }
@@ -2605,8 +2830,10 @@ gg_status gg_permute_tiles(gg_lattice *L, uint64_t seed) {
   GG_HIP(shuffle(L->d_tiles, L->n_tiles));
   GG_HIP(shuffle(L->d_strips, L->n_strips));
   GG_HIP(shuffle(L->d_seg_strips, L->n_seg_strips));
-  GG_HIP(shuffle(L->d_strips4, L->n_strips4));
-  GG_HIP(shuffle(L->d_seg_strips4, L->n_seg_strips4));
+  for (const PipeStrips &p : L->pipe) {
+    GG_HIP(shuffle(p.d_main, p.n_main));
+    GG_HIP(shuffle(p.d_seg, p.n_seg));
+  }
   GG_HIP(shuffle(L->d_cde_tiles, L->n_cde_tiles));
   GG_HIP(shuffle(L->d_cde_tiles4, L->n_cde_tiles4));
   gg_drop_cde_graphs(L);

@@ -187,9 +187,9 @@ class Lattice:
     def set_two_step(self, fuse: int = 3, strip_h: int = 6) -> None:
         """Two steps per pass over memory (fuse = 2: walking strips of
         strip_h rows; 3, the default: row-parallel tiles of 6 or 14 rows with
-        the boundary kernel apart; 4: the same in one kernel), four steps per
-        pass in runs of 8k steps (fuse = 5; other runs as fuse = 3) or
-        single steps (fuse = 1); include/gg.h,
+        the boundary kernel apart; 4: the same in one kernel), four or eight
+        steps per pass in runs of 4k steps (fuse = 5; other runs as fuse = 3)
+        or single steps (fuse = 1); include/gg.h,
         gg_set_two_step."""
         A.call("gg_set_two_step", self._h, int(fuse), int(strip_h))
 
@@ -422,8 +422,8 @@ class Batch:
         return dict(zip(("tile_x", "tile_y", "persist", "fuse", "rows"), [x.value for x in v]))
 
     def set_two_step(self, fuse: int = 4, rows: int = 6) -> None:
-        """Two-step passes over all members (fuse 3 or 4), four-step passes
-        (fuse 5) or single steps (fuse 1);
+        """Two-step passes over all members (fuse 3 or 4), passes of four or
+        eight steps (fuse 5) or single steps (fuse 1);
         include/gg.h, gg_batch_set_two_step."""
         A.call("gg_batch_set_two_step", self._h, int(fuse), int(rows))
 
