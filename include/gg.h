@@ -378,21 +378,19 @@ gg_status gg_set_phase_fields(gg_lattice *lat, const int32_t *slots, int32_t n);
  * to the velocity the coupled step's fluid has at that step, the compound
  * equals the coupled step's. Asynchronous; replays graphs of graph_chunk
  * steps (gg_set_launch). GG_ERR_STATE if a phase's slot was never set.
- * Steps from an even t go in two-step passes (see gg_set_cde_launch) while
+ * Steps from an even t go in passes of several (see gg_set_cde_launch) while
  * the second plane set exists (gg_set_two_step with fuse >= 2, the
  * default); the result is the same bit for bit either way. */
 gg_status gg_cde_step(gg_lattice *lat, int64_t n);
 
-/* Launch form of gg_cde_step: rows = 6 or 14 (the default) runs pairs of
- * steps as one pass over memory, one work-group of rows + 2 wavefronts per
- * tile of 62 columns x rows, which reads the compound state and the field
- * once and writes the state two steps later into the second plane set
- * (the compound planes only); rows = -6 or -10 runs runs of 8k steps in
- * passes of four steps (one work-group of -rows + 6 wavefronts per tile of
- * 58 columns x -rows rows with a three-node halo; lattices with pressure
- * segments, and the last four steps of a run of 8k + 4, in two-step passes
- * of 6-row tiles); rows = 0 keeps to single steps. GG_ERR_ARG for other
- * values. Every form gives the single steps' result bit for bit. */
+/* Launch form of gg_cde_step: rows = 14 (the default), 6, -6 or -10 runs pairs
+ * of passes of eight steps, then of four and of two, each of which reads the
+ * compound state and the field once and writes the state that many steps
+ * later into the second plane set (the compound planes only): one wavefront
+ * per strip of 50 columns, the strips' rows chosen by the library. Lattices
+ * with pressure segments run two-step passes over tiles of 14 rows (rows =
+ * 14) or 6 rows (the others). rows = 0 keeps to single steps. GG_ERR_ARG for
+ * other values. Every form gives the single steps' result bit for bit. */
 gg_status gg_set_cde_launch(gg_lattice *lat, int32_t rows);
 
 /* Number of fluid nodes and launched tiles. */

@@ -26,6 +26,34 @@ __device__ __forceinline__ PhaseNow phase_at(CDesc &L, int64_t t) {
   return {L.phase_open[k], L.phase_cin[k], L.phase_cin_f[k], k};
 }
 
+// The phases in force during the steps t .. t + N - 1, and whether they are
+// one (one division for all).
+template <int N> struct Phases {
+  PhaseNow ph[N];
+  bool one;
+  __device__ __forceinline__ Phases(CDesc &L, int64_t t) {
+    ph[0] = phase_at(L, t);
+    one = true;
+    int64_t tau = 0;
+    if (L.n_phases != 0) {
+      tau = (t - L.t_origin) % L.period;
+      if (tau < 0) tau += L.period;
+      const int k = ph[0].index;
+      one = tau + N <= (k + 1 < L.n_phases ? L.phase_start[k + 1] : L.period);
+    }
+#pragma unroll
+    for (int s = 1; s < N; ++s) ph[s] = ph[0];
+    if (one) return;
+    int k = ph[0].index;
+#pragma unroll
+    for (int s = 1; s < N; ++s) {
+      if (++tau == L.period) tau = k = 0;
+      while (k + 1 < L.n_phases && L.phase_start[k + 1] <= tau) ++k;
+      ph[s] = {L.phase_open[k], L.phase_cin[k], L.phase_cin_f[k], k};
+    }
+  }
+};
+
 // Inlet parameters of segment s in the compute type T (pre-rounded for FP32).
 template <class T> struct SegT;
 template <> struct SegT<double> {
@@ -244,10 +272,8 @@ using Flux = FluxT<double>;
 // of the columns x0 - 1 .. x0 + 62), the row count of a tile or strip kept
 // in its flags above bit 8, lane shifts that carry a population one column
 // right (from_left) or left (from_right), and the test whether x - e_j is
-// not fluid for a node with link code lc (j = 1..8). The four-step pass
-// owns 58 columns (lanes 3..60 of the columns x0 - 3 .. x0 + 60).
+// not fluid for a node with link code lc (j = 1..8).
 constexpr int STRIP_W = 62;
-constexpr int STRIP4_W = 58;
 __device__ __forceinline__ int strip_rows(int flags) { return flags >> 8; }
 template <class T> __device__ __forceinline__ T from_left(T v) { return __shfl_up(v, 1); }
 template <class T> __device__ __forceinline__ T from_right(T v) { return __shfl_down(v, 1); }

@@ -51,20 +51,13 @@
 #include "gg_device.h"
 #include "gg_kernels.h"
 #include "gg_node.h"
+#include "gg_strip.h"
 
 #include <type_traits>
 
 namespace gg {
 
 namespace {
-
-// The value of the lane to the left, to the right; `edge` where there is none.
-__device__ __forceinline__ uint32_t lane_shr(uint32_t v, uint32_t edge) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x138, 0xf, 0xf, false);
-}
-__device__ __forceinline__ uint32_t lane_shl(uint32_t v, uint32_t edge) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x130, 0xf, 0xf, false);
-}
 
 // Two populations of a node as they cross LDS, rounded to the storage type;
 // join: two stored elements side by side.
@@ -294,18 +287,9 @@ __global__ void __launch_bounds__(NS * 64)
   __shared__ uint32_t msk[SEG ? MR : 1][SEG ? 64 : 1];
   const int lane = (int)(threadIdx.x & 63);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  // the segment strips (the longest to run) first, dealt to the XCDs one by
-  // one; then each XCD a contiguous run of the others
-  const int b = (int)blockIdx.x, seg_blocks = (n_seg + 7) & ~7;
-  int tile = b;
-  const Tile *list = seg_tiles;
-  if (b >= seg_blocks) {
-    list = tiles;
-    tile = ((b - seg_blocks) & 7) * per_xcd + ((b - seg_blocks) >> 3);
-    if (tile >= n_tiles) return;  // the whole work-group, as below
-  } else if (tile >= n_seg) {
-    return;
-  }
+  const Tile *list;
+  int tile;
+  if (!strip_of((int)blockIdx.x, seg_tiles, n_seg, tiles, n_tiles, per_xcd, list, tile)) return;
   const GG_CONST Tile &tl = ((const GG_CONST Tile *)list)[tile];
   CDesc &L = ((CDesc *)descs)[tl.inst];
   const int nx = L.nx, ny = L.ny;

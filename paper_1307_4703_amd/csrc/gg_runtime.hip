@@ -117,8 +117,8 @@ void gg_free_device(gg_lattice *L) {
                   L->d_flux, L->d_acc, L->d_desc, L->d_tiles, L->d_aux_tiles, L->d_strips,
                   L->d_seg_strips, L->pipe[0].d_main, L->pipe[0].d_seg, L->pipe[1].d_main,
                   L->pipe[1].d_seg, L->d_partial, L->d_ufield,
-                  L->d_cde_tiles, L->d_cde_tiles4, L->d_press, L->d_wall, L->d_wall_links,
-                  L->d_wall_save,
+                  L->d_cde_tiles, L->cde_walk.d_main, L->cde_walk.d_seg,
+                  L->d_press, L->d_wall, L->d_wall_links, L->d_wall_save,
                   L->d_mon};
   for (void *p : ptrs)
     if (p) (void)dev_free(L, p);
@@ -2658,53 +2658,81 @@ gg_status gg_set_phase_fields(gg_lattice *L, const int32_t *slots, int32_t n) {
 gg_status gg_set_cde_launch(gg_lattice *L, int32_t rows) {
   if (!L) return fail(GG_ERR_ARG, "lattice is NULL");
   if (rows != 0 && rows != 6 && rows != 14 && rows != -6 && rows != -10)
-    return fail(GG_ERR_ARG, "rows must be 0, 6, 14 (two-step passes) or -6, -10 (four-step passes)");
+    return fail(GG_ERR_ARG, "rows must be 6, 14, -6, -10 (passes) or 0 (single steps)");
   GG_HIP(hipStreamSynchronize(L->stream));
   L->cde_rows = rows;
   gg_drop_cde_graphs(L);
   return GG_OK;
 }
 
-// Tile lists of the compound-only passes for the current row count: the
-// two-step pass's (6 rows when the four-step pass is on) and the four-step
-// pass's (58 columns, segment flag for a link within two nodes of the
-// tile, in vertical stripes per XCD as the coupled four-step pass's).
+// Rows per strip of the compound-only walk: a strip of `rows` rows takes
+// steps rows + steps (steps - 1) row collisions one after another on its
+// SIMD, and SIMDs with several strips take them about one after another too.
+// (Us a step: 2048 x 1024 gradient generator FP32 2.5 with this rule's rows,
+// 2.6 with 8, 3.0 with 16, 4.7 with 32; 410 x 205 2.25-2.3 with 2..8.)
+static int cde_walk_rows(int64_t strip_rows, int steps, int simds) {
+  int best = 128;
+  double best_cost = 0.0;
+  for (int rows : {2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64, 96, 128}) {
+    const double rounds = (double)strip_rows / rows * 1.03 / simds;
+    const double cost = (rounds > 4.0 ? rounds + 0.5 : std::ceil(rounds)) *
+                        (steps * rows + steps * (steps - 1) + 8);
+    if (best_cost == 0.0 || cost < best_cost) {
+      best = rows;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// Work lists of the compound-only passes: strips of the walk or, with pressure
+// segments, tiles of the two-step pass.
 static gg_status cde_tiles(gg_lattice *L) {
   if (L->cde_rows == 0 || L->cde_tiles_rows == L->cde_rows) return GG_OK;
-  std::vector<Tile> list, unused, list4;
-  L->cde_halo_seg = has_pressure(L);
-  build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, false, list, unused, L->cde_halo_seg);
-  if (L->cde_rows < 0) {
-    build_strips(L, -L->cde_rows, 0, false, list4, unused, 2, 58);
-    std::stable_sort(list4.begin(), list4.end(), [&](const Tile &a, const Tile &b) {
-      const int sa = (int)((int64_t)a.x0 * 8 / L->nx), sb = (int)((int64_t)b.x0 * 8 / L->nx);
-      return sa != sb ? sa < sb : (a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0);
-    });
-  }
   if (L->d_cde_tiles) GG_HIP(dev_free(L, L->d_cde_tiles));
-  if (L->d_cde_tiles4) GG_HIP(dev_free(L, L->d_cde_tiles4));
-  L->d_cde_tiles = L->d_cde_tiles4 = nullptr;
-  L->n_cde_tiles = (int)list.size();
-  L->n_cde_tiles4 = (int)list4.size();
-  L->cde_tiles_rows = 0;
-  if (!list.empty()) {
-    GG_HIP(dev_alloc(L, (void **)&L->d_cde_tiles, list.size() * sizeof(Tile)));
-    GG_HIP(hipMemcpy(L->d_cde_tiles, list.data(), list.size() * sizeof(Tile), hipMemcpyHostToDevice));
+  L->d_cde_tiles = nullptr;
+  L->n_cde_tiles = L->cde_tiles_rows = 0;
+  PipeStrips &w = L->cde_walk;
+  for (Tile *d : {w.d_main, w.d_seg})
+    if (d) GG_HIP(dev_free(L, d));
+  w = PipeStrips();
+  auto put = [&](const std::vector<Tile> &list, Tile *&d, int &count) -> gg_status {
+    if (list.empty()) return GG_OK;
+    GG_HIP(dev_alloc(L, (void **)&d, list.size() * sizeof(Tile)));
+    GG_HIP(hipMemcpy(d, list.data(), list.size() * sizeof(Tile), hipMemcpyHostToDevice));
+    count = (int)list.size();
+    return GG_OK;
+  };
+  std::vector<Tile> list, seg;
+  gg_status st;
+  L->cde_halo_seg = has_pressure(L);
+  if (L->cde_halo_seg) {
+    build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, false, list, seg, 1);
+    st = put(list, L->d_cde_tiles, L->n_cde_tiles);
+  } else {
+    int cus = 256;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device);
+    // (the halo of a pass wraps once)
+    const int axis = std::min(L->p.periodic_x ? L->nx : 8, L->p.periodic_y ? L->ny : 8);
+    w.plan.steps = axis >= 8 ? 8 : axis >= 4 ? 4 : axis >= 2 ? 2 : 0;
+    if (w.plan.steps > 0) {
+      w.plan.rows = cde_walk_rows(pipe_strip_rows(L, CDE_WALK_W), w.plan.steps, 4 * cus);
+      build_pipe(L, w.plan.rows, 0, CDE_WALK_W, w.plan.halo(), list, seg);
+    }
+    st = put(list, w.d_main, w.n_main);
+    if (st == GG_OK) st = put(seg, w.d_seg, w.n_seg);
   }
-  if (!list4.empty()) {
-    GG_HIP(dev_alloc(L, (void **)&L->d_cde_tiles4, list4.size() * sizeof(Tile)));
-    GG_HIP(hipMemcpy(L->d_cde_tiles4, list4.data(), list4.size() * sizeof(Tile), hipMemcpyHostToDevice));
-  }
+  if (st != GG_OK) return st;
   L->cde_tiles_rows = L->cde_rows;
   return GG_OK;
 }
 
 // n compound-only steps from a lattice whose counter reads t0 (host mirror),
 // then the counter advances by n. With passes on (cde_rows != 0 and the
-// second plane set present), the steps from an even t go in pairs of
-// passes (8 steps in four-step passes, then 4 in two-step passes) that end
-// in the first plane set; an odd-t first step and the leftover run as
-// single steps.
+// second plane set present), the steps from an even t go in pairs of passes
+// that end in the first plane set: the walk's, of 8 steps, then of 4, then of
+// 2, or with pressure segments two-step ones; an odd-t first step and the
+// leftover run as single steps.
 static hipError_t launch_cde_steps(gg_lattice *L, int64_t t0, int64_t n, hipStream_t st) {
   hipError_t e = hipSuccess;
   int64_t dt = 0;
@@ -2720,23 +2748,20 @@ static hipError_t launch_cde_steps(gg_lattice *L, int64_t t0, int64_t n, hipStre
         e = launch_rescale(L->storage, L->d_desc, L->d_press, L->n_press, (int)dt, false, st);
       ++dt;
     }
-    if (L->cde_rows < 0 && !press) {
-      // four-step passes in pairs (ending in the first plane set)
-      const int64_t p4 = (n - dt) / 8 * 2;
-      for (int64_t k = 0; k < p4 && e == hipSuccess; ++k)
-        e = launch_cde_tile4(L->storage, L->pairs, -L->cde_rows, L->d_desc, L->d_cde_tiles4,
-                             L->n_cde_tiles4, (int)(k & 1), (int)(dt + 4 * k), st);
-      dt += 4 * p4;
-    }
-    const int64_t passes = (n - dt) / 4 * 2;
+    const PipeStrips &w = L->cde_walk;
+    for (int steps = w.plan.steps; steps >= 2 && w.n_main + w.n_seg > 0; steps /= 2)
+      for (; n - dt >= 2 * steps && e == hipSuccess; dt += 2 * steps)
+        for (int k = 0; k < 2 && e == hipSuccess; ++k)
+          e = launch_cde_walk(L->storage, L->pairs, L->d_desc, w.d_seg, w.n_seg, w.d_main, w.n_main, k,
+                              (int)dt + k * steps, steps, st);
+    const int64_t passes = press ? (n - dt) / 4 * 2 : 0;
     // (pressure: each pass after the first rescales the state it loads, the
     // kernel the state the last one leaves, in pop_b after dir 0)
     const bool at_load = press && L->cde_halo_seg;
     for (int64_t k = 0; k < passes && e == hipSuccess; ++k) {
       e = launch_cde_tile2(L->storage, L->pairs, L->cde_rows < 0 ? 6 : L->cde_rows, L->d_desc,
                            L->d_cde_tiles, L->n_cde_tiles,
-                           (int)(k & 1) | (at_load && k > 0 ? 2 : 0), (int)(dt + 2 * k), st,
-                           press);
+                           (int)(k & 1) | (at_load && k > 0 ? 2 : 0), (int)(dt + 2 * k), st);
       if (e == hipSuccess && press && (!at_load || k == passes - 1))
         e = launch_rescale(L->storage, L->d_desc, L->d_press, L->n_press, (int)(dt + 2 * k + 1),
                            false, st, (k & 1) == 0);
@@ -2771,7 +2796,7 @@ gg_status gg_cde_step(gg_lattice *L, int64_t n) {
       return fail(GG_ERR_STATE, "velocity field slot " + std::to_string(s) + " of phase " +
                                     std::to_string(k) + " was never set");
   }
-  if ((st = cde_tiles(L)) != GG_OK || (st = pressure_nodes(L)) != GG_OK ||
+  if ((st = pressure_nodes(L)) != GG_OK || (st = cde_tiles(L)) != GG_OK ||
       (st = wall_nodes(L)) != GG_OK)
     return st;
   int64_t left = n;
@@ -2835,7 +2860,8 @@ gg_status gg_permute_tiles(gg_lattice *L, uint64_t seed) {
     GG_HIP(shuffle(p.d_seg, p.n_seg));
   }
   GG_HIP(shuffle(L->d_cde_tiles, L->n_cde_tiles));
-  GG_HIP(shuffle(L->d_cde_tiles4, L->n_cde_tiles4));
+  GG_HIP(shuffle(L->cde_walk.d_main, L->cde_walk.n_main));
+  GG_HIP(shuffle(L->cde_walk.d_seg, L->cde_walk.n_seg));
   gg_drop_cde_graphs(L);
   if (L->graph_exec) (void)hipGraphExecDestroy(L->graph_exec);
   if (L->graph) (void)hipGraphDestroy(L->graph);
