@@ -15,6 +15,7 @@
 // segment, dL/domega_g per work-group.
 #include "gg_adjoint.h"
 #include "gg_device.h"
+#include "gg_strip.h"
 
 namespace gg {
 
@@ -34,16 +35,10 @@ __device__ __forceinline__ Ph phase_of(CDesc &L, int64_t t) {
   return {L.phase_open[k], L.phase_cin[k]};
 }
 
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
 // Work-group sum into one value (every thread of the group must call).
 template <int BS>
 __device__ __forceinline__ double block_sum(double v, double *lds) {
-  v = wsum(v);
+  v = wave_sum(v);
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) lds[wave] = v;
   __syncthreads();
@@ -148,9 +143,9 @@ struct AdjAcc {
       unsigned long long pend = __ballot(seg >= 0);
       while (pend) {
         const int lead = __ffsll(pend) - 1;
-        const int sg = __shfl(seg, lead);
+        const int sg = __builtin_amdgcn_readlane(seg, lead);
         const bool mine = seg == sg;
-        const double a = wsum(mine ? v : 0.0);
+        const double a = wave_sum(mine ? v : 0.0);
         if ((int)__lane_id() == lead) atomicAdd(dcin + sg, a);
         pend &= ~__ballot(mine);
       }
@@ -428,7 +423,7 @@ __global__ void __launch_bounds__((R + 2) * 64)
   }
   if (seg) acc.flush_cin(dcin);
   // dL/domega_g: one partial sum per tile
-  const double v = wsum(acc.dw);
+  const double v = wave_sum(acc.dw);
   if (lane == 0) lds_sum[w] = v;
   __syncthreads();
   if (threadIdx.x == 0) {

@@ -64,8 +64,9 @@ __device__ __forceinline__ void strip_two_steps(const LatDesc *__restrict__ desc
   const int64_t t = *(const GG_CONST int64_t *)L.t + dt;
   PhaseNow ph1{0u, nullptr}, ph2{0u, nullptr};
   if (SEG) {
-    ph1 = phase_at(L, t);
-    ph2 = phase_at(L, t + 1);
+    const Phases<2> ph(L, t);
+    ph1 = ph.ph[0];
+    ph2 = ph.ph[1];
   }
   const Planes<W> src(dir ? L.pop_b : L.pop, L.plane, PAIRS);  // (the lattice's layout)
   const Planes<W> dst(dir ? L.pop : L.pop_b, L.plane, PAIRS);
@@ -267,8 +268,9 @@ __global__ void __launch_bounds__((R + 2) * 64)
     const bool seg = SEG && (tl.flags & TILE_TOUCHES_SEGMENT) != 0;
     PhaseNow ph1{0u, nullptr}, ph2{0u, nullptr};
     if (seg) {
-      ph1 = phase_at(L, t);
-      ph2 = phase_at(L, t + 1);
+      const Phases<2> ph(L, t);
+      ph1 = ph.ph[0];
+      ph2 = ph.ph[1];
     }
     const int dsel = PRESS ? (dir & 1) : dir;
     // (the layout is the lattice's, PAIRS: known at compile time)

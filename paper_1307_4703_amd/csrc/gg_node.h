@@ -6,6 +6,7 @@
 #pragma once
 
 #include "gg_device.h"
+#include "gg_strip.h"
 
 namespace gg {
 
@@ -141,13 +142,6 @@ template <class T> __device__ __forceinline__ T e_dot_u(int i, T ux, T uy) {
   }
 }
 
-// Sum over the 64 lanes of a wavefront; every lane must be active.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
@@ -166,7 +160,7 @@ __device__ __forceinline__ void flush_flux(double *flux, int sa, double ma, doub
     unsigned long long pend = __ballot(seg >= 0);
     while (pend) {
       const int lead = __ffsll(pend) - 1;
-      const int s = __shfl(seg, lead);
+      const int s = __builtin_amdgcn_readlane(seg, lead);
       const bool mine = seg == s;
       const double a = wave_sum(mine ? dm : 0.0);
       const double b = wave_sum(mine ? dc : 0.0);
@@ -275,8 +269,8 @@ using Flux = FluxT<double>;
 // not fluid for a node with link code lc (j = 1..8).
 constexpr int STRIP_W = 62;
 __device__ __forceinline__ int strip_rows(int flags) { return flags >> 8; }
-template <class T> __device__ __forceinline__ T from_left(T v) { return __shfl_up(v, 1); }
-template <class T> __device__ __forceinline__ T from_right(T v) { return __shfl_down(v, 1); }
+template <class T> __device__ __forceinline__ T from_left(T v) { return lane_shr(v); }
+template <class T> __device__ __forceinline__ T from_right(T v) { return lane_shl(v); }
 __device__ __forceinline__ bool src_solid(uint8_t lc, int j) { return (lc >> (OPP[j] - 1)) & 1; }
 
 // Fused multiply-add with one rounding, for both compute types.
@@ -452,79 +446,6 @@ __device__ __forceinline__ void open_link(const NodeK<T> &N, const SG &sg, int j
   }
 }
 
-// Collision of fluid node (x, y) with link code lc, from the deviations f, g
-// of step t (phase ph): post-collision deviations pf, pg, and in_f[j],
-// in_g[j], the value that arrives at (x, y) along direction j at t + 1 when
-// x - e_j is not fluid (bounce-back from a wall or closed valve, or the rule
-// of an open segment). Fluxes through open segments go into fx when count.
-// nbr, when given, holds the mask values of the cells x + e_k (k = 1..8,
-// wrapped on periodic axes, walls beyond the others) loaded beforehand, as
-// bytes k - 1 of nbr[0] (k = 1..4) and nbr[1] (k = 5..8).
-//
-// PRESS compiles the pressure-boundary rule in. The two-step passes leave it
-// out unless the lattice has pressure segments (their own instantiation),
-// which keeps the node's pre-collision populations out of the others'
-// register budget and their control flow as it was; without it an open
-// pressure link would take the outlet rule.
-template <class T, bool PRESS = true, class FX = Flux>
-__device__ __forceinline__ void collide_node(const NodeK<T> &N, CDesc &L, int x, int y,
-                                             uint8_t lc, bool seg_tile, const PhaseNow &ph,
-                                             const T *f, const T *g, T *pf, T *pg, T *in_f,
-                                             T *in_g, FX &fx, bool count,
-                                             const uint32_t *nbr = nullptr) {
-  // Every kernel that advances the lattice inlines this function; the fused
-  // multiply-adds are written out and no other contraction is allowed, so
-  // each of them rounds exactly the same way whatever code surrounds it.
-#pragma clang fp contract(off)
-  T rho, drho, ux, uy;
-  node_velocity<T>(N, f, rho, drho, ux, uy);
-  const T usq = fmad(ux, ux, uy * uy);
-
-  fluid_collide<T>(N, f, rho, drho, ux, uy, usq, pf);
-  compound_collide<T>(N, L, x, y, g, ux, uy, pg);
-
-  // Value arriving at x along direction j when x - e_j is not fluid: the
-  // bounced population f*(x, opp j) for a wall or closed valve; open
-  // segments overwrite below. (For fluid x - e_j the same slot carries
-  // f*(x, opp j) to that neighbour.)
-#pragma unroll
-  for (int j = 0; j < 9; ++j) in_f[j] = pf[OPP[j]];
-#pragma unroll
-  for (int j = 0; j < 5; ++j) in_g[j] = pg[OPP[j]];
-
-  if (seg_tile && lc != 0) {
-    const int nx = L.nx, ny = L.ny, pitch = L.pitch;
-    // (every rule below is written for the deviations; w_j = w_opp(j), so
-    // the rest parts cancel except where noted)
-#pragma unroll
-    for (int j = 1; j < 9; ++j) {
-      if (!((lc >> (OPP[j] - 1)) & 1)) continue;  // x - e_j is fluid
-      int sx = x - EX[j], sy = y - EY[j];
-      bool inside = true;
-      if (sx < 0 || sx >= nx) {
-        if (L.periodic_x) sx = (sx + nx) % nx; else inside = false;
-      }
-      if (sy < 0 || sy >= ny) {
-        if (L.periodic_y) sy = (sy + ny) % ny; else inside = false;
-      }
-      const int code = nbr ? (int)((nbr[(OPP[j] - 1) >> 2] >> (8 * ((OPP[j] - 1) & 3))) & 0xFFu)
-                     : inside ? (int)((const GG_GLOBAL uint8_t *)L.mask)[L.node0 + sy * pitch + sx]
-                              : GG_MASK_WALL;
-      if (code < GG_FIRST_SEGMENT) continue;
-      const int s = code - GG_FIRST_SEGMENT;
-      if (!((ph.open >> s) & 1u)) continue;  // closed valve: a wall
-      T vf, vg = T(0);
-      open_link<T, PRESS>(N, SegRef<T>{L, ph, s}, j, x, y, f[j], j < 5 ? g[j] : T(0), pf[OPP[j]],
-                          j < 5 ? pg[OPP[j]] : T(0), j < 5 ? pg[j] : T(0), ux, uy, usq, vf, vg);
-      const T dm = vf - pf[OPP[j]];
-      const T dc = (j < 5) ? vg - pg[OPP[j]] : T(0);
-      in_f[j] = vf;
-      if (j < 5) in_g[j] = vg;
-      if (count) fx.add(s, dm, dc);
-    }
-  }
-}
-
 // The collision alone: post-collision deviations and the velocity (and its
 // square) it was made with.
 template <class T>
@@ -577,6 +498,63 @@ __device__ __forceinline__ void links_in_place(const NodeK<T> &N, CDesc &L, int 
       pend &= ~__ballot(mine);
     }
   }
+}
+
+// Collision of fluid node (x, y) with link code lc, from the deviations f, g
+// of step t (phase ph): post-collision deviations pf, pg, and in_f[j],
+// in_g[j], the value that arrives at (x, y) along direction j at t + 1 when
+// x - e_j is not fluid (bounce-back from a wall or closed valve, or the rule
+// of an open segment). Fluxes through open segments go into fx when count.
+// nbr, when given, holds the mask values of the cells x + e_k (k = 1..8,
+// wrapped on periodic axes, walls beyond the others) loaded beforehand, as
+// bytes k - 1 of nbr[0] (k = 1..4) and nbr[1] (k = 5..8).
+//
+// PRESS compiles the pressure-boundary rule in. The two-step passes leave it
+// out unless the lattice has pressure segments (their own instantiation),
+// which keeps the node's pre-collision populations out of the others'
+// register budget and their control flow as it was; without it an open
+// pressure link would take the outlet rule.
+template <class T, bool PRESS = true, class FX = Flux>
+__device__ __forceinline__ void collide_node(const NodeK<T> &N, CDesc &L, int x, int y,
+                                             uint8_t lc, bool seg_tile, const PhaseNow &ph,
+                                             const T *f, const T *g, T *pf, T *pg, T *in_f,
+                                             T *in_g, FX &fx, bool count,
+                                             const uint32_t *nbr = nullptr) {
+  // Every kernel that advances the lattice inlines this function or calls its
+  // two halves; the fused multiply-adds are spelled out, so that all of them
+  // do the same arithmetic.
+  uint32_t cells[2] = {0u, 0u};
+  if (seg_tile && lc != 0 && lc != NOT_FLUID) {  // (ahead of the collision: the loads overlap it)
+    if (nbr) {
+      cells[0] = nbr[0];
+      cells[1] = nbr[1];
+    } else {
+      const Neigh nb(L, x, y);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int dx = x + EX[k + 1], dy = y + EY[k + 1];
+        const bool inside = (L.periodic_x || (dx >= 0 && dx < L.nx)) &&
+                            (L.periodic_y || (dy >= 0 && dy < L.ny));
+        const uint32_t m = ((const GG_GLOBAL uint8_t *)L.mask)[nb.idx[k + 1]];
+        cells[k >> 2] |= (inside ? m : (uint32_t)GG_MASK_WALL) << (8 * (k & 3));
+      }
+    }
+  }
+  T ux, uy, usq;
+  collide_only<T>(N, L, x, y, f, g, pf, pg, ux, uy, usq);
+  if (seg_tile) {
+    const uint32_t links = lc != NOT_FLUID ? lc : 0u;
+    if (__any(links != 0)) {
+      SegHeld<T> held;
+      links_in_place<T, PRESS>(N, L, x, y, links, cells, ph, f, g, pf, pg, ux, uy, usq, held, fx,
+                               count);
+    }
+  }
+  // the value arriving at x along direction j when x - e_j is not fluid
+#pragma unroll
+  for (int j = 0; j < 9; ++j) in_f[j] = pf[OPP[j]];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) in_g[j] = pg[OPP[j]];
 }
 
 // The same with the lattice's constants read from the descriptor as they are
