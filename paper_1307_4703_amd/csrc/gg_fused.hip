@@ -225,6 +225,13 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// Wavefronts a SIMD must hold in the boundary tiles' kernel: with 80 registers
+// three work-groups of 6-row tiles fit a CU in FP32, two with a few more (2048
+// x 1024 gradient generator in one kernel, 64 steps: 540 us, and 580 with 86).
+constexpr int tile2_waves(bool seg, bool press, size_t bytes) {
+  return !seg ? 1 : bytes == 8 ? (press ? 3 : 4) : press ? 5 : 6;
+}
+
 // Row-parallel form of the same two steps, for lattices too small to keep
 // the GPU busy with walking strips: one work-group per tile of 62 columns x
 // R rows (at most; the row count is in the tile flags), R + 2 wavefronts,
@@ -245,7 +252,8 @@ __global__ void __launch_bounds__(256)
 // moments as the collision), to the planes of the compute type at tape0
 // (step t) and tape1 (step t + 1), as the single step's tape does.
 template <class S, bool SEG, int R, bool PRESS, bool TAPE, bool PAIRS>
-__global__ void __launch_bounds__((R + 2) * 64)
+__global__ void
+    __launch_bounds__((R + 2) * 64, tile2_waves(SEG, PRESS, sizeof(typename Pop<S>::T)))
     k_tile2(const LatDesc *__restrict__ descs, const Tile *__restrict__ tiles, int n_tiles,
             int per_xcd, int dir, int dt, void *__restrict__ tape0, void *__restrict__ tape1) {
   using P = Pop<S>;
@@ -253,6 +261,7 @@ __global__ void __launch_bounds__((R + 2) * 64)
   using W = typename P::W;
   __shared__ T lds_up[R + 2][4][64];
   __shared__ T lds_dn[R + 2][4][64];
+  __shared__ FluxRow flux[SEG ? R + 2 : 1];
   const int lane = (int)(threadIdx.x & 63);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int nb = 8 * per_xcd;
@@ -268,6 +277,7 @@ __global__ void __launch_bounds__((R + 2) * 64)
     const bool seg = SEG && (tl.flags & TILE_TOUCHES_SEGMENT) != 0;
     PhaseNow ph1{0u, nullptr}, ph2{0u, nullptr};
     if (seg) {
+      flux_clear(flux[SEG ? w : 0], lane);
       const Phases<2> ph(L, t);
       ph1 = ph.ph[0];
       ph2 = ph.ph[1];
@@ -374,8 +384,8 @@ __global__ void __launch_bounds__((R + 2) * 64)
     // (the first step's fluxes leave before the barrier: the accumulators
     // are not held across it)
     if (seg) {
-      fx.flush((double *)L.flux);
-      if (PRESS) fr.flush((double *)L.flux);
+      fx.flush_row(flux[SEG ? w : 0]);
+      if (PRESS) fr.flush_row(flux[SEG ? w : 0]);
     }
     __syncthreads();
 
@@ -441,10 +451,14 @@ __global__ void __launch_bounds__((R + 2) * 64)
         second_step<S, false, false, FluxT<T>>(L, dst, x, y, lc, ph2, sf, sg, fx);
     }
     if (seg) {
-      fx.flush((double *)L.flux);
-      if (PRESS) fr.flush((double *)L.flux);
+      fx.flush_row(flux[SEG ? w : 0]);
+      if (PRESS) fr.flush_row(flux[SEG ? w : 0]);
     }
     __syncthreads();  // the LDS rows are reused by the next tile
+    if (seg) {
+      if (w == 0) flux_total(flux, R + 2, lane, (double *)L.flux);
+      if (b + (int)gridDim.x < nb) __syncthreads();
+    }
   }
 }
 

@@ -34,7 +34,7 @@ namespace gg {
 // also write the node's state before the step to `tape` for the adjoint,
 // planes of the compute type with the populations' plane stride: dg_0..4,
 // then u_x, u_y (from the same moments as the collision).
-template <class S, bool ODD, bool PAIRS, bool TAPE = false>
+template <class S, int BS, bool ODD, bool PAIRS, bool TAPE = false>
 __device__ __forceinline__ void step_tile(const LatDesc *__restrict__ descs,
                                           const Tile *__restrict__ tiles, int tile,
                                           int tx_shift, int dt, void *tape = nullptr) {
@@ -117,7 +117,15 @@ __device__ __forceinline__ void step_tile(const LatDesc *__restrict__ descs,
     }
   }
 
-  if (seg_tile) fx.flush((double *)L.flux);
+  if (seg_tile) {
+    __shared__ FluxRow flux[BS / 64];
+    const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    flux_clear(flux[w], lane);
+    fx.flush_row(flux[w]);
+    __syncthreads();
+    if (w == 0) flux_total(flux, BS / 64, lane, (double *)L.flux);
+    __syncthreads();  // (the table is the next tile's)
+  }
 }
 
 // The fused step over a tile list. Work-groups are dealt to the 8 XCDs
@@ -132,7 +140,7 @@ __global__ void __launch_bounds__(BS)
   const int nb = 8 * per_xcd;
   for (int b = blockIdx.x; b < nb; b += gridDim.x) {
     const int tile = (b & 7) * per_xcd + (b >> 3);
-    if (tile < n_tiles) step_tile<S, ODD, PAIRS>(descs, tiles, tile, tx_shift, dt);
+    if (tile < n_tiles) step_tile<S, BS, ODD, PAIRS>(descs, tiles, tile, tx_shift, dt);
   }
 }
 
@@ -144,7 +152,7 @@ __global__ void __launch_bounds__(BS)
   const int nb = 8 * per_xcd;
   for (int b = blockIdx.x; b < nb; b += gridDim.x) {
     const int tile = (b & 7) * per_xcd + (b >> 3);
-    if (tile < n_tiles) step_tile<S, ODD, PAIRS, true>(descs, tiles, tile, tx_shift, dt, tape);
+    if (tile < n_tiles) step_tile<S, BS, ODD, PAIRS, true>(descs, tiles, tile, tx_shift, dt, tape);
   }
 }
 

@@ -149,9 +149,11 @@ __device__ __forceinline__ double wave_max(double v) {
 }
 
 // Add per-lane boundary fluxes (up to two segments per lane, seg < 0 for
-// none) into the FP64 accumulators: one atomic per segment and wavefront.
-__device__ __forceinline__ void flush_flux(double *flux, int sa, double ma, double ca, int sb,
-                           double mb, double cb) {
+// none) to a table of (mass, solute) per segment: add(entry, value) is called
+// by one lane, once per entry and wavefront.
+template <class F>
+__device__ __forceinline__ void flush_flux(int sa, double ma, double ca, int sb, double mb,
+                                           double cb, F &&add) {
 #pragma unroll
   for (int slot = 0; slot < 2; ++slot) {
     const int seg = slot ? sb : sa;
@@ -165,12 +167,28 @@ __device__ __forceinline__ void flush_flux(double *flux, int sa, double ma, doub
       const double a = wave_sum(mine ? dm : 0.0);
       const double b = wave_sum(mine ? dc : 0.0);
       if ((int)__lane_id() == lead) {
-        atomicAdd(flux + 2 * s, a);
-        atomicAdd(flux + 2 * s + 1, b);
+        add(2 * s, a);
+        add(2 * s + 1, b);
       }
       pend &= ~__ballot(mine);
     }
   }
+}
+
+// A work-group's boundary fluxes in LDS, a row of the table per wavefront: the
+// wavefronts add to their rows, and one of them adds the sums to the FP64
+// accumulators at the end (all of a lattice's boundary nodes add to a few
+// words of memory, about 13 ns apiece: a two-step pass with an atomic per
+// wavefront and step took 107 us on a 1024 x 1024 channel in FP32, now 28).
+using FluxRow = double[2 * GG_MAX_SEGMENTS];
+__device__ __forceinline__ void flux_clear(FluxRow &row, int lane) {
+  if (lane < 2 * GG_MAX_SEGMENTS) row[lane] = 0.0;
+}
+__device__ __forceinline__ void flux_total(const FluxRow *rows, int n, int lane, double *flux) {
+  if (lane >= 2 * GG_MAX_SEGMENTS) return;
+  double v = 0.0;
+  for (int w = 0; w < n; ++w) v += rows[w][lane];
+  if (v != 0.0) atomicAdd(flux + lane, v);
 }
 
 // Element offset of x + e_k for k = 0..8: wrapped along periodic axes,
@@ -253,9 +271,15 @@ template <class A> struct FluxT {
       sb = s; mb += (A)dm; cb += (A)dc;
     }
   }
-  // every lane of the wavefront must call this
+  // every lane of the wavefront must call these
   __device__ __forceinline__ void flush(double *flux) {
-    flush_flux(flux, sa, (double)ma, (double)ca, sb, (double)mb, (double)cb);
+    flush_to([&](int k, double v) { atomicAdd(flux + k, v); });
+  }
+  __device__ __forceinline__ void flush_row(FluxRow &row) {
+    flush_to([&](int k, double v) { row[k] += v; });
+  }
+  template <class F> __device__ __forceinline__ void flush_to(F &&add) {
+    flush_flux(sa, (double)ma, (double)ca, sb, (double)mb, (double)cb, add);
     sa = sb = -1;
     ma = ca = mb = cb = A(0);
   }

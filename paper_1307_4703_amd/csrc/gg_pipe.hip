@@ -285,6 +285,7 @@ __global__ void __launch_bounds__(NS * 64)
   // x - 1, x, x + 1 of each lane, as bytes 0..2; row r at r mod MR
   constexpr int MR = NS <= 4 ? 16 : 32;
   __shared__ uint32_t msk[SEG ? MR : 1][SEG ? 64 : 1];
+  __shared__ FluxRow flux[SEG ? NS : 1];
   const int lane = (int)(threadIdx.x & 63);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const Tile *list;
@@ -311,7 +312,10 @@ __global__ void __launch_bounds__(NS * 64)
   }
 
   PhaseNow ph{0u, nullptr};
-  if (seg) ph = phase_at(L, *(const GG_CONST int64_t *)L.t + dt + w);
+  if (seg) {
+    ph = phase_at(L, *(const GG_CONST int64_t *)L.t + dt + w);
+    flux_clear(flux[SEG ? w : 0], lane);
+  }
   NodeK<T> N(L);
   N.hold();
   FluxT<T> fx;
@@ -337,7 +341,7 @@ __global__ void __launch_bounds__(NS * 64)
             byte(up, 2) | byte(up, 0) << 8 | byte(dn, 0) << 16 | byte(dn, 2) << 24};
         links_in_place<T, false, FluxT<T>>(N, L, x, y, link ? lc : 0u, nbr, ph, f, g, pf, pg, ux,
                                            uy, usq, held_seg, fx, own);
-        fx.flush((double *)L.flux);
+        fx.flush_row(flux[SEG ? w : 0]);
       }
     }
   };
@@ -493,6 +497,7 @@ __global__ void __launch_bounds__(NS * 64)
       });
   }
   for (; k < iters; ++k) __syncthreads();
+  if (SEG && seg && last) flux_total(flux, ns, lane, (double *)L.flux);
 }
 
 // Calls `with` with the kernel made for max_steps (8 for FP32 only, as the

@@ -90,6 +90,8 @@ struct gg_lattice {
   // tile lists built with the halo-inclusive segment flag (pressure
   // segments: the passes rescale the boundary nodes as they load them)
   bool tiles_halo_seg = false, cde_halo_seg = false;
+  // the pass's tiles are in one list, and some touch a segment
+  bool strips_whole = false, strips_seg = false;
   bool strip_flux_ok = true;  // no vertical node pair links to > 2 segments
   gg::Tile *d_strips = nullptr;      // strips without segment links
   int n_strips = 0;

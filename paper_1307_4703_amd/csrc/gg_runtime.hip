@@ -609,6 +609,16 @@ static hipError_t launch_pipes(const PipeStrips *lists, int64_t n, F &&launch) {
   return e;
 }
 
+// Tiles up to which fuse 3 takes the boundary tiles in the one kernel with the
+// others: up to about a round of them (the boundary kernel holds 12 of its
+// wavefronts of 6-row tiles a CU), a second kernel's launch, fork and join cost
+// more than the registers of the boundary rules. Us for 8 steps launched one by
+// one and for 64 from a graph, two kernels -> one, FP32: 128 x 64 channel 140
+// and 512 -> 57 and 369, gradient generator 410 x 205 130 and 428 -> 42 and
+// 253, 2048 x 1024 (1300 tiles) 140 and 558 -> 79 and 540, 4096 x 2048 (5200
+// tiles) 278 and 1852 -> 239 and 1810, but FP16 168 and 968 -> 151 and 1085.
+constexpr int ONE_KERNEL_TILES = 3072;
+
 gg_status gg_rebuild_tiles(gg_lattice *L) {
   std::vector<Tile> t;
   build_tiles(L, L->tile_x, L->tile_y, 0, t);
@@ -623,7 +633,18 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
   // with pressure segments the one-kernel pass rescales the state it loads
   // in every tile that collides a boundary node, halo included
   L->tiles_halo_seg = L->fuse == 4 && has_pressure(L);
-  build_strips(L, L->strip_h, 0, L->fuse != 4, sv, ss, L->tiles_halo_seg ? 1 : 0);
+  // the one-kernel form (fuse 4, and fuse 3 on small lattices): all tiles of
+  // one height in one list
+  bool whole = L->fuse == 4;
+  if (L->fuse == 3 && !has_pressure(L)) {
+    build_strips(L, L->strip_h, 0, false, sv, ss, 0);
+    whole = (int)sv.size() <= ONE_KERNEL_TILES;
+    if (!whole) sv.clear();
+  }
+  if (sv.empty()) build_strips(L, L->strip_h, 0, !whole, sv, ss, L->tiles_halo_seg ? 1 : 0);
+  L->strips_whole = whole;
+  L->strips_seg = false;
+  for (const Tile &tl : sv) L->strips_seg = L->strips_seg || (tl.flags & TILE_TOUCHES_SEGMENT) != 0;
   if (L->d_strips) (void)dev_free(L, L->d_strips);
   if (L->d_seg_strips) (void)dev_free(L, L->d_seg_strips);
   L->d_strips = L->d_seg_strips = nullptr;
@@ -963,7 +984,8 @@ static bool has_pressure(const gg_lattice *L) {
 static gg_status pressure_nodes(gg_lattice *L) {
   if (!L->press_dirty) return GG_OK;
   // the tile lists mark the tiles that must rescale what they load
-  if (L->tiles_halo_seg != (L->fuse == 4 && has_pressure(L)) || L->tiles4 != pass4_ok(L)) {
+  if (L->tiles_halo_seg != (L->fuse == 4 && has_pressure(L)) || L->tiles4 != pass4_ok(L) ||
+      (L->fuse == 3 && L->strips_whole && has_pressure(L))) {
     gg_status st = gg_rebuild_tiles(L);
     if (st != GG_OK) return st;
   }
@@ -1227,12 +1249,12 @@ static hipError_t launch_pass(gg_lattice *L, int dir, int dt, hipStream_t st) {
   // (with the four-step pass on, the two-step passes of leftover steps are
   // not the dominant kernel: profiled apart, kind 4)
   const int kind = L->tiles4 && pass4_ok(L) ? 4 : 0;
-  if (L->fuse == 4) {  // one kernel with the boundary rules for every tile
+  if (L->strips_whole && L->fuse >= 3) {  // one kernel for every tile
     e = prof_begin(L, st, pidx);
     if (e == hipSuccess)
-      e = launch_tile2(L->storage, L->pairs, true, L->strip_h, L->d_desc, L->d_strips,
+      e = launch_tile2(L->storage, L->pairs, L->fuse == 4 || L->strips_seg, L->strip_h, L->d_desc, L->d_strips,
                        L->n_strips, dir, dt, st, press);
-    if (e == hipSuccess) e = prof_end(L, st, pidx, 0);
+    if (e == hipSuccess) e = prof_end(L, st, pidx, kind);
     return e;
   }
   auto run = [&](bool seg, const Tile *list, int n, hipStream_t s) {
@@ -1925,8 +1947,8 @@ gg_status gg_adjoint(gg_lattice *L, int64_t n, int64_t s, const double *weight,
           char *t0p = (char *)tp + (size_t)(j + 2 * q) * slot;
           char *t1p = t0p + slot;
           const int dt = (int)(j + 2 * q);
-          if (L->fuse == 4) {
-            e = launch_tile2(L->storage, L->pairs, true, L->strip_h, sd, L->d_strips, L->n_strips, q, dt, rs,
+          if (L->strips_whole) {
+            e = launch_tile2(L->storage, L->pairs, L->fuse == 4 || L->strips_seg, L->strip_h, sd, L->d_strips, L->n_strips, q, dt, rs,
                              false, t0p, t1p);
           } else {
             if (L->n_seg_strips > 0)
