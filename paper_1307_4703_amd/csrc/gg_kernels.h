@@ -103,9 +103,12 @@ hipError_t launch_relayout(gg_storage s, void *src, void *dst, int64_t plane, in
 hipError_t launch_init(gg_storage s, const LatDesc *d, const Tile *tiles, int n_tiles,
                        int tx_shift, const double *rho, const double *ux,
                        const double *uy, const double *c, hipStream_t st);
-hipError_t launch_read(gg_storage s, const LatDesc *d, const Tile *tiles, int n_tiles,
-                       int tx_shift, double *rho, double *ux, double *uy, double *c,
-                       double *f, double *g, hipStream_t st);
+// The fields and populations of the nx x ny cells, each pointer null or an
+// output (NaN and 0 off the fluid); with tiles only the fluid cells of these 64
+// x 4 tiles, the outputs filled before.
+hipError_t launch_read(gg_storage s, const LatDesc *d, int nx, int ny, double *rho, double *ux,
+                       double *uy, double *c, double *f, double *g, const Tile *tiles, int n_tiles,
+                       hipStream_t st);
 // FP64 diagnostics into acc[0..5] (mass, solute, max|u|, region max|u|,
 // non-finite count, fluid count) through partial[6 * groups], groups =
 // n_tiles (one work-group per tile) or, with max_groups > 0, at most

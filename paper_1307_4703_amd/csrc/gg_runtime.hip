@@ -1534,6 +1534,10 @@ static gg_status gg_read_impl(gg_lattice *L, double *rho, double *ux, double *uy
   const int64_t len[6] = {n, n, n, n, 9 * n, 5 * n};
   const double fillv[6] = {NAN, NAN, NAN, NAN, 0.0, 0.0};
   double *dev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  // mostly walls, and outputs beyond the Infinity Cache (256 MB): filled first
+  int64_t cells = 0;
+  for (int q = 0; q < 6; ++q) cells += user[q] ? len[q] : 0;
+  const bool fill = cells > ((int64_t)32 << 20) && 2 * L->n_fluid < n;
   gg_status st = GG_OK;
   for (int q = 0; q < 6; ++q) {
     if (!user[q]) continue;
@@ -1545,14 +1549,14 @@ static gg_status gg_read_impl(gg_lattice *L, double *rho, double *ux, double *uy
     } else {
       dev[q] = user[q];
     }
-    if (launch_fill(dev[q], len[q], fillv[q], L->stream) != hipSuccess) {
+    if (fill && launch_fill(dev[q], len[q], fillv[q], L->stream) != hipSuccess) {
       st = fail(GG_ERR_HIP, "fill of a read-back buffer failed");
       break;
     }
   }
   if (st == GG_OK) {
-    hipError_t e = launch_read(L->storage, L->d_desc, L->d_aux_tiles, L->n_aux_tiles, 6,
-                               dev[0], dev[1], dev[2], dev[3], dev[4], dev[5], L->stream);
+    hipError_t e = launch_read(L->storage, L->d_desc, L->nx, L->ny, dev[0], dev[1], dev[2], dev[3],
+                               dev[4], dev[5], fill ? L->d_aux_tiles : nullptr, L->n_aux_tiles, L->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
     if (e == hipSuccess && where == GG_HOST)
       for (int q = 0; q < 6 && e == hipSuccess; ++q)
