@@ -133,6 +133,8 @@ struct gg_lattice {
   gg::Tile *d_cde_tiles = nullptr;
   PipeStrips cde_walk;
   int n_cde_tiles = 0, cde_tiles_rows = 0;
+  // buffers of the last adjoint run and their sizes, kept for the next
+  std::vector<std::pair<void *, size_t>> adjoint_kept;
   hipGraph_t cde_graph[2] = {nullptr, nullptr};
   hipGraphExec_t cde_exec[2] = {nullptr, nullptr};
   // fluid nodes owned by the tiles of the pass's two lists
