@@ -36,7 +36,8 @@ CSRC = os.path.join(ROOT, "paper_1307_4703_amd", "csrc")
 # sources of the dominant kernel (the two-step pass); the counters in
 # profiles/traffic.json hold for the hash of these files
 KERNEL_SRC = [os.path.join(CSRC, f)
-              for f in ("gg_device.h", "gg_node.h", "gg_fused.hip", "gg_pipe.hip", "gg_cde.hip")]
+              for f in ("gg_device.h", "gg_strip.h", "gg_node.h", "gg_fused.hip", "gg_pipe.hip",
+                        "gg_cde.hip")]
 
 
 def log(msg):
@@ -79,10 +80,8 @@ FORMS = {"gg2048_f32": (5, 6), "gg2048_f16": (4, 6), "gg8192_f16": (3, 6),
          "allfluid8192_f64": (5, 6), "gg2048_f64": (5, 6), "straight_f64": (4, 6)}
 # the adjoint leg's lattice (2048 x 1024 FP32): the one-kernel two-step
 # form, whose taped recomputation passes are one kernel as well (the
-# four-step pass has no taped form; its lattices recompute in the two
-# kernels of fuse 3: the forward sweep gains, 0.138 against 0.164 s over
-# 20000 steps on this GPU, the whole gradient loses, 0.588-0.592 against
-# 0.569-0.580 s)
+# pipelined passes have no taped form: their lattices recompute in two
+# kernels a pass)
 ADJOINT_FORM = (4, 6)
 
 
@@ -563,7 +562,8 @@ def counters_leg(leg, tile, chunk_unused=0):
         for name, steps, flow, rows in CDE_LEG:
             r = cde_bench(name, 16, 4, rows, 0)
             ct = CTYPE[r["storage"]]
-            kern, grid = (f"k_cde_walk<{ct}, 8," if rows else f"k_cde<{ct},"), None
+            seg = "true" if workload(name).segments else "false"
+            kern, grid = (f"k_cde_walk<{ct}, 8, {seg}," if rows else f"k_cde<{ct},"), None
             # one trip of the compound's bytes per launch (a pass moves them
             # once for its eight steps)
             manifest["cde:" + name] = {"kernel": kern, "grid": grid, "units": r["n_fluid"],

@@ -3,8 +3,8 @@
 Candidates are tile shapes (tile_x x tile_y nodes per work-group) of the
 single steps, the forms of the two-step pass (walking strips, row-parallel
 tiles with the boundary rules in a kernel of their own or in the one
-kernel) and the four-step pass, for batches persistent grid sizes, and for the compound-only step
-the row count of its two-step tiles. Each candidate is timed
+kernel) and the pipelined passes, for batches persistent grid sizes, and for
+the compound-only step passes or single steps. Each candidate is timed
 on the GPU with HIP events over a few graph-replayed steps (the lattices
 advance while being tuned, so tune before the run or on a copy). Results are cached in a JSON
 file keyed by the device name, storage type and the lattices' shapes and
