@@ -262,11 +262,13 @@ template <> struct Pop<__half> {
   // the value a store followed by a load gives back
   static __device__ __forceinline__ T rt(T v) { return __half2float(to_half(v)); }
   // Two values rounded by one packed conversion (v_cvt_pk_f16_f32: round to
-  // nearest even, as the single conversion). A packed conversion is never
-  // folded into the arithmetic before it, so it needs no barrier.
+  // nearest even, as the single conversion), behind the same barrier: where
+  // the two halves are used apart the compiler takes the conversion apart
+  // again and folds it like the single one.
   using H2 = _Float16 __attribute__((ext_vector_type(2)));
   using F2 = float __attribute__((ext_vector_type(2)));
   static __device__ __forceinline__ H2 to_half2(T a, T b) {
+    asm("" : "+v"(a), "+v"(b));
     F2 v;
     v[0] = a;
     v[1] = b;
