@@ -90,9 +90,13 @@ struct gg_lattice {
   // tile lists built with the halo-inclusive segment flag (pressure
   // segments: the passes rescale the boundary nodes as they load them)
   bool tiles_halo_seg = false, cde_halo_seg = false;
-  // the pass's tiles are in one list, and some touch a segment
-  bool strips_whole = false, strips_seg = false;
   bool strip_flux_ok = true;  // no vertical node pair links to > 2 segments
+  // the two-step pass's tiles, in one buffer (d_pass_tiles): all of them, for
+  // the one-kernel form (none if the lattice does not take it; whole_seg: some
+  // touch a segment), and split for the form with the boundary tiles apart
+  gg::Tile *d_pass_tiles = nullptr, *d_whole = nullptr;
+  int n_whole = 0;
+  bool whole_seg = false;
   gg::Tile *d_strips = nullptr;      // strips without segment links
   int n_strips = 0;
   gg::Tile *d_seg_strips = nullptr;  // strips with segment links (2 rows each)

@@ -114,8 +114,8 @@ void gg_free_device(gg_lattice *L) {
   L->graph_exec = nullptr;
   L->graph = nullptr;
   void *ptrs[] = {L->d_pop, L->d_pop_b, L->d_link, L->d_mask, L->d_region, L->d_R, L->d_t,
-                  L->d_flux, L->d_acc, L->d_desc, L->d_tiles, L->d_aux_tiles, L->d_strips,
-                  L->d_seg_strips, L->pipe[0].d_main, L->pipe[0].d_seg, L->pipe[1].d_main,
+                  L->d_flux, L->d_acc, L->d_desc, L->d_tiles, L->d_aux_tiles,
+                  L->d_pass_tiles, L->pipe[0].d_main, L->pipe[0].d_seg, L->pipe[1].d_main,
                   L->pipe[1].d_seg, L->d_partial, L->d_ufield,
                   L->d_cde_tiles, L->cde_walk.d_main, L->cde_walk.d_seg,
                   L->d_press, L->d_wall, L->d_wall_links, L->d_wall_save,
@@ -237,21 +237,24 @@ static void build_tiles(const gg_lattice *L, int tx, int ty, int inst,
 // columns of a band (rows y0 .. y0 + h - 1), listed band by band from left
 // to right: horizontally adjacent strips store into the same cache lines at
 // their common edge every row, so they go to the same XCD (a contiguous run
-// of the list) and run side by side in one work-group. With split, a band
-// piece with a link to a boundary segment is cut into 2-row strips and
-// those with segment links go to the second list; otherwise it stays whole
-// in the first. Flags: strip height << 8 | segment bit.
-static void build_strips(const gg_lattice *L, int h, int inst, bool split, std::vector<Tile> &main,
-                         std::vector<Tile> &seg, int halo = 0) {
-  const int width = 62;
+// of the list) and run side by side in one work-group. Flags: strip height
+// << 8 | segment bit.
+constexpr int STRIP_WIDTH = 62;
+// Does a strip hold a fluid node (any), one that links to a segment (sg).
+static void scan_strip(const gg_lattice *L, int x0, int y0, int rows, bool &any, bool &sg) {
+  any = sg = false;
+  for (int y = y0; y < std::min(y0 + rows, L->ny); ++y)
+    for (int x = x0; x < std::min(x0 + STRIP_WIDTH, L->nx); ++x) {
+      if (L->link[L->nid(x, y)] == NOT_FLUID) continue;
+      any = true;
+      if (L->touches_seg[(size_t)y * L->nx + x]) sg = true;
+    }
+}
+static void build_strips(const gg_lattice *L, int h, int inst, std::vector<Tile> &out,
+                         int halo = 0) {
+  const int width = STRIP_WIDTH;
   auto scan = [&](int x0, int y0, int rows, bool &any, bool &sg) {
-    any = sg = false;
-    for (int y = y0; y < std::min(y0 + rows, L->ny); ++y)
-      for (int x = x0; x < std::min(x0 + width, L->nx); ++x) {
-        if (L->link[L->nid(x, y)] == NOT_FLUID) continue;
-        any = true;
-        if (L->touches_seg[(size_t)y * L->nx + x]) sg = true;
-      }
+    scan_strip(L, x0, y0, rows, any, sg);
     // halo 1 (pressure segments, rescaled at load): also when a node of
     // the one-node halo the tile collides touches a segment (wrapped on
     // periodic axes)
@@ -296,21 +299,29 @@ static void build_strips(const gg_lattice *L, int h, int inst, bool split, std::
       for (int x0 = run.first; x0 < run.second; x0 += width) {
         bool any, sg;
         scan(x0, y0, h, any, sg);
-        if (!any) continue;
-        if (!sg || !split) {
-          main.push_back(Tile{inst, x0, y0, (h << 8) | (sg ? TILE_TOUCHES_SEGMENT : 0)});
-          continue;
-        }
-        for (int yy = y0; yy < std::min(y0 + h, L->ny); yy += 2) {
-          const int rows = std::min(2, y0 + h - yy);
-          scan(x0, yy, rows, any, sg);
-          if (!any) continue;
-          if (sg)
-            seg.push_back(Tile{inst, x0, yy, (rows << 8) | TILE_TOUCHES_SEGMENT});
-          else
-            main.push_back(Tile{inst, x0, yy, rows << 8});
-        }
+        if (any) out.push_back(Tile{inst, x0, y0, (h << 8) | (sg ? TILE_TOUCHES_SEGMENT : 0)});
       }
+  }
+}
+
+// The strips of build_strips (no halo) as two lists: one with links to a
+// segment is cut into 2-row strips, and those with such links go to the
+// second list, everything else to the first.
+static void split_strips(const gg_lattice *L, const std::vector<Tile> &all, std::vector<Tile> &main,
+                         std::vector<Tile> &seg) {
+  for (const Tile &t : all) {
+    if (!(t.flags & TILE_TOUCHES_SEGMENT)) {
+      main.push_back(t);
+      continue;
+    }
+    const int h = t.flags >> 8;
+    for (int y = t.y0; y < std::min(t.y0 + h, L->ny); y += 2) {
+      const int rows = std::min(2, t.y0 + h - y);
+      bool any, sg;
+      scan_strip(L, t.x0, y, rows, any, sg);
+      if (!any) continue;
+      (sg ? seg : main).push_back(Tile{t.inst, t.x0, y, (rows << 8) | (sg ? TILE_TOUCHES_SEGMENT : 0)});
+    }
   }
 }
 
@@ -630,36 +641,36 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
     GG_HIP(dev_alloc(L, (void **)&L->d_tiles, t.size() * sizeof(Tile)));
     GG_HIP(hipMemcpy(L->d_tiles, t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice));
   }
-  std::vector<Tile> sv, ss;
+  // the two-step pass's tiles: whole, for the one-kernel form (fuse 4, and
+  // fuse 3 on small lattices without pressure segments), and split, for the
+  // form with the boundary tiles apart, in one buffer
+  std::vector<Tile> all, main, seg;
   // with pressure segments the one-kernel pass rescales the state it loads
   // in every tile that collides a boundary node, halo included
   L->tiles_halo_seg = L->fuse == 4 && has_pressure(L);
-  // the one-kernel form (fuse 4, and fuse 3 on small lattices): all tiles of
-  // one height in one list
-  bool whole = L->fuse == 4;
-  if (L->fuse == 3 && !has_pressure(L)) {
-    build_strips(L, L->strip_h, 0, false, sv, ss, 0);
-    whole = (int)sv.size() <= ONE_KERNEL_TILES;
-    if (!whole) sv.clear();
+  build_strips(L, L->strip_h, 0, all, L->tiles_halo_seg ? 1 : 0);
+  L->whole_seg = L->fuse == 4;
+  for (const Tile &tl : all) L->whole_seg = L->whole_seg || (tl.flags & TILE_TOUCHES_SEGMENT) != 0;
+  if (L->fuse != 4) {
+    split_strips(L, all, main, seg);
+    if (L->fuse != 3 || (int)all.size() > ONE_KERNEL_TILES) all.clear();
   }
-  if (sv.empty()) build_strips(L, L->strip_h, 0, !whole, sv, ss, L->tiles_halo_seg ? 1 : 0);
-  L->strips_whole = whole;
-  L->strips_seg = false;
-  for (const Tile &tl : sv) L->strips_seg = L->strips_seg || (tl.flags & TILE_TOUCHES_SEGMENT) != 0;
-  if (L->d_strips) (void)dev_free(L, L->d_strips);
-  if (L->d_seg_strips) (void)dev_free(L, L->d_seg_strips);
-  L->d_strips = L->d_seg_strips = nullptr;
-  L->n_strips = (int)sv.size();
-  L->n_seg_strips = (int)ss.size();
-  L->strips_fluid = owned_fluid(L, sv);
-  L->seg_strips_fluid = owned_fluid(L, ss);
-  if (!sv.empty()) {
-    GG_HIP(dev_alloc(L, (void **)&L->d_strips, sv.size() * sizeof(Tile)));
-    GG_HIP(hipMemcpy(L->d_strips, sv.data(), sv.size() * sizeof(Tile), hipMemcpyHostToDevice));
-  }
-  if (!ss.empty()) {
-    GG_HIP(dev_alloc(L, (void **)&L->d_seg_strips, ss.size() * sizeof(Tile)));
-    GG_HIP(hipMemcpy(L->d_seg_strips, ss.data(), ss.size() * sizeof(Tile), hipMemcpyHostToDevice));
+  if (L->d_pass_tiles) (void)dev_free(L, L->d_pass_tiles);
+  L->d_pass_tiles = L->d_whole = L->d_strips = L->d_seg_strips = nullptr;
+  L->n_whole = (int)all.size();
+  L->n_strips = (int)main.size();
+  L->n_seg_strips = (int)seg.size();
+  L->strips_fluid = owned_fluid(L, main);
+  L->seg_strips_fluid = owned_fluid(L, seg);
+  std::vector<Tile> lists(all);
+  lists.insert(lists.end(), main.begin(), main.end());
+  lists.insert(lists.end(), seg.begin(), seg.end());
+  if (!lists.empty()) {
+    GG_HIP(dev_alloc(L, (void **)&L->d_pass_tiles, lists.size() * sizeof(Tile)));
+    GG_HIP(hipMemcpy(L->d_pass_tiles, lists.data(), lists.size() * sizeof(Tile), hipMemcpyHostToDevice));
+    L->d_whole = L->d_pass_tiles;
+    L->d_strips = L->d_whole + L->n_whole;
+    L->d_seg_strips = L->d_strips + L->n_strips;
   }
   // the pipelined passes' strips
   L->tiles4 = pass4_ok(L);
@@ -985,8 +996,7 @@ static bool has_pressure(const gg_lattice *L) {
 static gg_status pressure_nodes(gg_lattice *L) {
   if (!L->press_dirty) return GG_OK;
   // the tile lists mark the tiles that must rescale what they load
-  if (L->tiles_halo_seg != (L->fuse == 4 && has_pressure(L)) || L->tiles4 != pass4_ok(L) ||
-      (L->fuse == 3 && L->strips_whole && has_pressure(L))) {
+  if (L->tiles_halo_seg != (L->fuse == 4 && has_pressure(L)) || L->tiles4 != pass4_ok(L)) {
     gg_status st = gg_rebuild_tiles(L);
     if (st != GG_OK) return st;
   }
@@ -1242,6 +1252,12 @@ static hipError_t prof_end(gg_lattice *L, hipStream_t st, long idx, int kind) {
   return hipEventRecord(L->prof_ev[idx + 1], st);
 }
 
+// The two-step pass takes all tiles in one kernel (with pressure segments only
+// as fuse 4: fuse 3 keeps the boundary kernel apart).
+static bool one_kernel(const gg_lattice *L) {
+  return L->n_whole > 0 && (L->fuse == 4 || !has_pressure(L));
+}
+
 static hipError_t launch_pass(gg_lattice *L, int dir, int dt, hipStream_t st) {
   hipError_t e = hipSuccess;
   const bool fork = L->n_seg_strips > 0 && L->n_strips > 0;
@@ -1250,11 +1266,11 @@ static hipError_t launch_pass(gg_lattice *L, int dir, int dt, hipStream_t st) {
   // (with the four-step pass on, the two-step passes of leftover steps are
   // not the dominant kernel: profiled apart, kind 4)
   const int kind = L->tiles4 && pass4_ok(L) ? 4 : 0;
-  if (L->strips_whole && L->fuse >= 3) {  // one kernel for every tile
+  if (one_kernel(L)) {
     e = prof_begin(L, st, pidx);
     if (e == hipSuccess)
-      e = launch_tile2(L->storage, L->pairs, L->fuse == 4 || L->strips_seg, L->strip_h, L->d_desc, L->d_strips,
-                       L->n_strips, dir, dt, st, press);
+      e = launch_tile2(L->storage, L->pairs, L->whole_seg, L->strip_h, L->d_desc, L->d_whole,
+                       L->n_whole, dir, dt, st, press);
     if (e == hipSuccess) e = prof_end(L, st, pidx, kind);
     return e;
   }
@@ -1511,10 +1527,11 @@ gg_status gg_step_profile(gg_lattice *L, int64_t n, gg_profile *out) {
   out->fuse = pass_ok(L) ? L->fuse : 1;
   out->rows = L->strip_h;
   out->steps_per_pass = 2;
-  out->pass_fluid = L->fuse == 4 ? L->n_fluid : L->strips_fluid;
-  out->pass_side_fluid = L->fuse == 4 ? 0 : L->seg_strips_fluid;
-  out->pass_tiles = L->n_strips;
-  out->pass_side_tiles = L->fuse == 4 ? 0 : L->n_seg_strips;
+  const bool one = one_kernel(L);
+  out->pass_fluid = one ? L->n_fluid : L->strips_fluid;
+  out->pass_side_fluid = one ? 0 : L->seg_strips_fluid;
+  out->pass_tiles = one ? L->n_whole : L->n_strips;
+  out->pass_side_tiles = one ? 0 : L->n_seg_strips;
   if (L->tiles4 && pass4_ok(L)) {  // the pipelined pass
     const PipeStrips &p = L->pipe[0];
     out->rows = p.plan.rows;
@@ -1854,9 +1871,9 @@ gg_status gg_adjoint(gg_lattice *L, int64_t n, int64_t s, const double *weight,
   // Where the lattice steps in two-step passes, the adjoint steps go in
   // pairs too (the adjoint of the pass) over 62 x 6 tiles of all fluid
   // nodes, flagged where the tile or its halo touches a segment.
-  std::vector<Tile> adj_tiles, adj_unused;
+  std::vector<Tile> adj_tiles;
   const bool adj_pass = L->fuse >= 3;
-  if (adj_pass) build_strips(L, 6, 0, false, adj_tiles, adj_unused, true);
+  if (adj_pass) build_strips(L, 6, 0, adj_tiles, 1);
   const int na = std::max({L->n_aux_tiles, (int)adj_tiles.size(), 1});
 
   AdjointBuffers B(L);
@@ -1973,9 +1990,9 @@ gg_status gg_adjoint(gg_lattice *L, int64_t n, int64_t s, const double *weight,
           char *t0p = (char *)tp + (size_t)(j + 2 * q) * slot;
           char *t1p = t0p + slot;
           const int dt = (int)(j + 2 * q);
-          if (L->strips_whole) {
-            e = launch_tile2(L->storage, L->pairs, L->fuse == 4 || L->strips_seg, L->strip_h, sd, L->d_strips, L->n_strips, q, dt, rs,
-                             false, t0p, t1p);
+          if (one_kernel(L)) {
+            e = launch_tile2(L->storage, L->pairs, L->whole_seg, L->strip_h, sd, L->d_whole, L->n_whole, q, dt,
+                             rs, false, t0p, t1p);
           } else {
             if (L->n_seg_strips > 0)
               e = launch_tile2(L->storage, L->pairs, true, 2, sd, L->d_seg_strips, L->n_seg_strips, q, dt, rs,
@@ -2470,8 +2487,14 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
   B->rows = rows;
   if (fuse == 1) return GG_OK;
   std::vector<Tile> sv, ss;
-  for (size_t k = 0; k < B->lats.size() && fuse != 5; ++k)
-    build_strips(B->lats[k], rows, (int)k, fuse != 4, sv, ss);
+  for (size_t k = 0; k < B->lats.size() && fuse != 5; ++k) {
+    std::vector<Tile> all;
+    build_strips(B->lats[k], rows, (int)k, all);
+    if (fuse == 4)
+      sv.insert(sv.end(), all.begin(), all.end());
+    else
+      split_strips(B->lats[k], all, sv, ss);
+  }
   B->n_strips = (int)sv.size();
   B->n_seg_strips = (int)ss.size();
   if (!sv.empty()) {
@@ -2755,7 +2778,7 @@ static gg_status cde_tiles(gg_lattice *L) {
   gg_status st;
   L->cde_halo_seg = has_pressure(L);
   if (L->cde_halo_seg) {
-    build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, false, list, seg, 1);
+    build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, list, 1);
     st = put(list, L->d_cde_tiles, L->n_cde_tiles);
   } else {
     int cus = 256;
@@ -2901,6 +2924,7 @@ gg_status gg_permute_tiles(gg_lattice *L, uint64_t seed) {
     return hipMemcpy(d, h.data(), h.size() * sizeof(Tile), hipMemcpyHostToDevice);
   };
   GG_HIP(shuffle(L->d_tiles, L->n_tiles));
+  GG_HIP(shuffle(L->d_whole, L->n_whole));
   GG_HIP(shuffle(L->d_strips, L->n_strips));
   GG_HIP(shuffle(L->d_seg_strips, L->n_seg_strips));
   for (const PipeStrips &p : L->pipe) {
