@@ -148,6 +148,7 @@ struct gg_lattice {
   // those of four steps for what passes of eight leave over
   PipeStrips pipe[2];
   bool tiles4 = false;  // the lists were built (pass4_ok held)
+  bool lists_ok = false;  // gg_rebuild_tiles went through
   // monitor: the FP64 reduction of gg_diagnostics launched after every
   // mon_every-th step (counted from mon_t0) into d_mon (8 totals, then the
   // 2 * GG_MAX_SEGMENTS flux accumulators copied at the same point)

@@ -631,16 +631,24 @@ static hipError_t launch_pipes(const PipeStrips *lists, int64_t n, F &&launch) {
 // tiles) 278 and 1852 -> 239 and 1810, but FP16 168 and 968 -> 151 and 1085.
 constexpr int ONE_KERNEL_TILES = 3072;
 
+// A call that fails on the way leaves no list behind (and no graph that holds
+// one); the next step builds them again (lists_ready).
 gg_status gg_rebuild_tiles(gg_lattice *L) {
+  L->lists_ok = false;
+  if (L->graph_exec) (void)hipGraphExecDestroy(L->graph_exec);
+  if (L->graph) (void)hipGraphDestroy(L->graph);
+  L->graph_exec = nullptr;
+  L->graph = nullptr;
   std::vector<Tile> t;
   build_tiles(L, L->tile_x, L->tile_y, 0, t);
   if (L->d_tiles) (void)dev_free(L, L->d_tiles);
   L->d_tiles = nullptr;
-  L->n_tiles = (int)t.size();
+  L->n_tiles = 0;
   if (!t.empty()) {
     GG_HIP(dev_alloc(L, (void **)&L->d_tiles, t.size() * sizeof(Tile)));
     GG_HIP(hipMemcpy(L->d_tiles, t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice));
   }
+  L->n_tiles = (int)t.size();
   // the two-step pass's tiles: whole, for the one-kernel form (fuse 4, and
   // fuse 3 on small lattices without pressure segments), and split, for the
   // form with the boundary tiles apart, in one buffer
@@ -657,9 +665,7 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
   }
   if (L->d_pass_tiles) (void)dev_free(L, L->d_pass_tiles);
   L->d_pass_tiles = L->d_whole = L->d_strips = L->d_seg_strips = nullptr;
-  L->n_whole = (int)all.size();
-  L->n_strips = (int)main.size();
-  L->n_seg_strips = (int)seg.size();
+  L->n_whole = L->n_strips = L->n_seg_strips = 0;
   L->strips_fluid = owned_fluid(L, main);
   L->seg_strips_fluid = owned_fluid(L, seg);
   std::vector<Tile> lists(all);
@@ -669,22 +675,23 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
     GG_HIP(dev_alloc(L, (void **)&L->d_pass_tiles, lists.size() * sizeof(Tile)));
     GG_HIP(hipMemcpy(L->d_pass_tiles, lists.data(), lists.size() * sizeof(Tile), hipMemcpyHostToDevice));
     L->d_whole = L->d_pass_tiles;
-    L->d_strips = L->d_whole + L->n_whole;
-    L->d_seg_strips = L->d_strips + L->n_strips;
+    L->d_strips = L->d_whole + all.size();
+    L->d_seg_strips = L->d_strips + main.size();
   }
+  L->n_whole = (int)all.size();
+  L->n_strips = (int)main.size();
+  L->n_seg_strips = (int)seg.size();
   // the pipelined passes' strips
   L->tiles4 = pass4_ok(L);
-  {
-    const gg_lattice *self[1] = {L};
-    const gg_status st = pipe_strips(self, L->tiles4 ? 1 : 0, L, L->pipe);
-    if (st != GG_OK) return st;
-  }
-  if (L->graph_exec) (void)hipGraphExecDestroy(L->graph_exec);
-  if (L->graph) (void)hipGraphDestroy(L->graph);
-  L->graph_exec = nullptr;
-  L->graph = nullptr;
+  const gg_lattice *self[1] = {L};
+  const gg_status st = pipe_strips(self, L->tiles4 ? 1 : 0, L, L->pipe);
+  if (st != GG_OK) return st;
+  L->lists_ok = true;
   return GG_OK;
 }
+
+// The lists of the launch form in force, after a call that failed to build them.
+static gg_status lists_ready(gg_lattice *L) { return L->lists_ok ? GG_OK : gg_rebuild_tiles(L); }
 
 static gg_status check_params(const gg_params *p) {
   if (!p) return fail(GG_ERR_ARG, "params is NULL");
@@ -1428,7 +1435,8 @@ gg_status gg_step(gg_lattice *L, int64_t n) {
   if (n < 0) return fail(GG_ERR_ARG, "n must be non-negative");
   gg_status st = check_segments(L);
   if (st != GG_OK) return st;
-  if ((st = pressure_nodes(L)) != GG_OK || (st = wall_nodes(L)) != GG_OK) return st;
+  if ((st = lists_ready(L)) != GG_OK || (st = pressure_nodes(L)) != GG_OK || (st = wall_nodes(L)) != GG_OK)
+    return st;
   if (L->mon_every <= 0) return step_run(L, n);
   int64_t left = n;
   while (left > 0) {
@@ -2479,11 +2487,11 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
   if (B->d_seg_strips) (void)hipFree(B->d_seg_strips);
   B->d_strips = B->d_seg_strips = nullptr;
   B->n_strips = B->n_seg_strips = 0;
+  B->fuse = 1;  // (until all lists are there: a call that fails leaves single steps)
   {
     const gg_status st = pipe_strips(B->lats.data(), fuse == 5 ? (int)B->lats.size() : 0, nullptr, B->pipe);
     if (st != GG_OK) return st;
   }
-  B->fuse = fuse;
   B->rows = rows;
   if (fuse == 1) return GG_OK;
   std::vector<Tile> sv, ss;
@@ -2495,8 +2503,6 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
     else
       split_strips(B->lats[k], all, sv, ss);
   }
-  B->n_strips = (int)sv.size();
-  B->n_seg_strips = (int)ss.size();
   if (!sv.empty()) {
     GG_HIP(hipMalloc(&B->d_strips, sv.size() * sizeof(Tile)));
     GG_HIP(hipMemcpy(B->d_strips, sv.data(), sv.size() * sizeof(Tile), hipMemcpyHostToDevice));
@@ -2510,6 +2516,9 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
     GG_HIP(hipEventCreateWithFlags(&B->ev_fork, hipEventDisableTiming));
     GG_HIP(hipEventCreateWithFlags(&B->ev_join, hipEventDisableTiming));
   }
+  B->n_strips = (int)sv.size();
+  B->n_seg_strips = (int)ss.size();
+  B->fuse = fuse;
   // replays run whole passes: a multiple of 4 steps, of 8 or 16 with fuse 5
   const int q = fuse == 5 ? 2 * B->pipe[0].plan.steps : 4;
   B->chunk = (B->chunk + q - 1) / q * q;
@@ -2536,6 +2545,7 @@ gg_status gg_step_timed(gg_lattice *L, int64_t n, double *ms_even, double *ms_od
   if (n < 1) return fail(GG_ERR_ARG, "n must be positive");
   gg_status st = check_segments(L);
   if (st != GG_OK) return st;
+  if ((st = lists_ready(L)) != GG_OK) return st;
   const int block = L->tile_x * L->tile_y;
   const int txs = ilog2(L->tile_x);
   std::vector<hipEvent_t> ev(2 * (size_t)n, nullptr);
@@ -2578,6 +2588,7 @@ gg_status gg_step2_timed(gg_lattice *L, int64_t n_pairs, double *ms_pass) {
   if (L->t & 1) return fail(GG_ERR_STATE, "the two-step pass starts on an even step");
   gg_status st = check_segments(L);
   if (st != GG_OK) return st;
+  if ((st = lists_ready(L)) != GG_OK) return st;
   const int64_t n = 2 * n_pairs;  // passes, even: the state ends in the first plane set
   std::vector<hipEvent_t> ev(2 * (size_t)n, nullptr);
   hipError_t e = hipSuccess;
