@@ -472,8 +472,10 @@ typedef struct gg_grads {
  * source gradient dL/dR is written to d_R (host, w*h doubles, row-major).
  * Device memory: about n/ckpt_every copies of the state plus ckpt_every
  * tape slots of 7 fields; GG_ERR_OOM if it does not fit. Up to 2 GiB of it
- * stay with the lattice for its next run, until that asks for other sizes or
- * the lattice is destroyed (none from a caller's allocator). */
+ * stay with the lattice for its next run, until that asks for other sizes,
+ * the lattice is destroyed, runs of other lattices keep theirs (2 GiB in all)
+ * or an allocation of the library fails without them (none from a caller's
+ * allocator). */
 gg_status gg_adjoint(gg_lattice *lat, int64_t n_steps, int64_t ckpt_every,
                      const double *weight, const double *target,
                      const int32_t *r_box, double *d_R, gg_grads *out);

@@ -137,7 +137,8 @@ struct gg_lattice {
   gg::Tile *d_cde_tiles = nullptr;
   PipeStrips cde_walk;
   int n_cde_tiles = 0, cde_tiles_rows = 0;
-  // buffers of the last adjoint run and their sizes, kept for the next
+  // buffers of the last adjoint run and their sizes, kept for the next (in
+  // the runtime's KeptBuffers, whose lock guards them)
   std::vector<std::pair<void *, size_t>> adjoint_kept;
   hipGraph_t cde_graph[2] = {nullptr, nullptr};
   hipGraphExec_t cde_exec[2] = {nullptr, nullptr};

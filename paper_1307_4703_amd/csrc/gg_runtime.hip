@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -46,13 +47,69 @@ int ilog2(int v) {
   return r;
 }
 
+// Buffers of adjoint runs that stay with their lattices for the next run
+// (gg_lattice::adjoint_kept), the longest kept first. All lattices of the
+// process together keep at most ADJOINT_KEEP bytes, and an allocation of the
+// library that fails gives them all back and tries again.
+constexpr size_t ADJOINT_KEEP = (size_t)2 << 30;
+struct KeptBuffers {
+  std::mutex mu;
+  std::vector<gg_lattice *> order;
+  static size_t bytes(const gg_lattice *L) {
+    size_t n = 0;
+    for (const auto &p : L->adjoint_kept) n += p.second;
+    return n;
+  }
+  static void release(gg_lattice *L) {
+    for (const auto &p : L->adjoint_kept) (void)hipFree(p.first);
+    L->adjoint_kept.clear();
+  }
+  // what L keeps, no longer kept
+  std::vector<std::pair<void *, size_t>> take(gg_lattice *L) {
+    std::lock_guard<std::mutex> lock(mu);
+    order.erase(std::remove(order.begin(), order.end(), L), order.end());
+    return std::move(L->adjoint_kept);
+  }
+  // L keeps bufs (from hipMalloc, at most ADJOINT_KEEP bytes)
+  void keep(gg_lattice *L, std::vector<std::pair<void *, size_t>> &&bufs) {
+    std::lock_guard<std::mutex> lock(mu);
+    L->adjoint_kept = std::move(bufs);
+    order.push_back(L);
+    size_t total = 0;
+    for (const gg_lattice *q : order) total += bytes(q);
+    while (total > ADJOINT_KEEP) {
+      total -= bytes(order.front());
+      release(order.front());
+      order.erase(order.begin());
+    }
+  }
+  bool release_all() {
+    std::lock_guard<std::mutex> lock(mu);
+    const bool any = !order.empty();
+    for (gg_lattice *L : order) release(L);
+    order.clear();
+    return any;
+  }
+};
+KeptBuffers &g_kept = *new KeptBuffers;  // (never destroyed: lattices may outlive static objects)
+
+hipError_t dev_malloc(void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && g_kept.release_all()) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 // Device memory of a lattice: from the caller's allocator when one was
 // given to gg_create_ex, else hipMalloc / hipFree. Memory goes back to the
 // caller's allocator only after the device is idle (as hipFree waits), so
 // no queued kernel still uses it when the allocator hands it out again.
 hipError_t dev_alloc(const gg_lattice *L, void **p, size_t bytes) {
-  if (!L->has_alloc) return hipMalloc(p, bytes);
+  if (!L->has_alloc) return dev_malloc(p, bytes);
   *p = bytes ? L->alloc.alloc(bytes, L->alloc.ctx) : nullptr;
+  if (!*p && bytes && g_kept.release_all()) *p = L->alloc.alloc(bytes, L->alloc.ctx);
   return (*p || !bytes) ? hipSuccess : hipErrorOutOfMemory;
 }
 
@@ -122,8 +179,7 @@ void gg_free_device(gg_lattice *L) {
                   L->d_mon};
   for (void *p : ptrs)
     if (p) (void)dev_free(L, p);
-  for (const auto &p : L->adjoint_kept) (void)dev_free(L, p.first);
-  L->adjoint_kept.clear();
+  for (const auto &p : g_kept.take(L)) (void)hipFree(p.first);
   for (hipEvent_t ev : L->prof_ev)
     if (ev) (void)hipEventDestroy(ev);
   L->prof_ev.clear();
@@ -555,7 +611,7 @@ static bool pass4_ok(const gg_lattice *L) {
 // lists[0..1], in device memory of `owner`'s allocator (null: hipMalloc).
 static gg_status pipe_strips(const gg_lattice *const *lats, int n, const gg_lattice *owner,
                              PipeStrips *lists) {
-  auto alloc = [&](void **q, size_t bytes) { return owner ? dev_alloc(owner, q, bytes) : hipMalloc(q, bytes); };
+  auto alloc = [&](void **q, size_t bytes) { return owner ? dev_alloc(owner, q, bytes) : dev_malloc(q, bytes); };
   for (int i = 0; i < 2; ++i) {
     PipeStrips &p = lists[i];
     for (Tile *d : {p.d_main, p.d_seg})
@@ -1820,19 +1876,18 @@ gg_status gg_info(const gg_lattice *L, int64_t *n_fluid, int64_t *n_tiles, int64
 // gigabyte in many pieces costs more than a short run: 25 ms for 112 steps of
 // an 821 x 413 FP64 lattice, 3.2 with kept buffers; 400 steps of a 1024 x 512
 // FP32 one 9.4 ms, and 20-30 in an unlucky process, 7.5 now.
-constexpr size_t ADJOINT_KEEP = (size_t)2 << 30;
 struct AdjointBuffers {
   gg_lattice *L;
   std::vector<std::pair<void *, size_t>> ptrs;
   size_t used = 0;
-  explicit AdjointBuffers(gg_lattice *lat) : L(lat) { ptrs.swap(L->adjoint_kept); }
+  explicit AdjointBuffers(gg_lattice *lat) : L(lat), ptrs(g_kept.take(lat)) {}
   ~AdjointBuffers() {
     (void)hipStreamSynchronize(L->stream);  // (an exit with an error)
     drop(used);
     size_t total = 0;
     for (const auto &p : ptrs) total += p.second;
     if (L->has_alloc || total > ADJOINT_KEEP) drop(0);
-    ptrs.swap(L->adjoint_kept);
+    if (!ptrs.empty()) g_kept.keep(L, std::move(ptrs));
   }
   void drop(size_t from) {
     for (size_t k = from; k < ptrs.size(); ++k) (void)dev_free(L, ptrs[k].first);
@@ -2240,12 +2295,12 @@ gg_status gg_batch_create(gg_lattice *const *lats, int32_t n, int32_t tile_x, in
     B->pop_b_created.push_back(descs[k].pop_b != nullptr);
   }
   hipError_t e = hipStreamSynchronize(B->stream);
-  if (e == hipSuccess) e = hipMalloc(&B->d_descs, n * sizeof(LatDesc));
+  if (e == hipSuccess) e = dev_malloc((void **)&B->d_descs, n * sizeof(LatDesc));
   if (e == hipSuccess) e = hipMemcpy(B->d_descs, descs.data(), n * sizeof(LatDesc), hipMemcpyHostToDevice);
   for (int g = 0; g < 2 && e == hipSuccess; ++g) {
     B->n_tiles[g] = (int)tiles[g].size();
     if (tiles[g].empty()) continue;
-    e = hipMalloc(&B->d_tiles[g], tiles[g].size() * sizeof(Tile));
+    e = dev_malloc((void **)&B->d_tiles[g], tiles[g].size() * sizeof(Tile));
     if (e == hipSuccess)
       e = hipMemcpy(B->d_tiles[g], tiles[g].data(), tiles[g].size() * sizeof(Tile), hipMemcpyHostToDevice);
   }
@@ -2276,7 +2331,7 @@ static gg_status batch_autotune(gg_lattice *const *lats, int32_t n, int32_t grap
     off[k + 1] = off[k] + (size_t)NPOP * lats[k]->plane * lats[k]->esize +
                  2 * GG_MAX_SEGMENTS * sizeof(double) + sizeof(int64_t);
   void *save = nullptr;
-  if (hipMalloc(&save, off[n]) != hipSuccess) return fail(GG_ERR_OOM, "autotune: state copies");
+  if (dev_malloc(&save, off[n]) != hipSuccess) return fail(GG_ERR_OOM, "autotune: state copies");
   struct Free {
     void *p;
     ~Free() { (void)hipFree(p); }
@@ -2504,11 +2559,11 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
       split_strips(B->lats[k], all, sv, ss);
   }
   if (!sv.empty()) {
-    GG_HIP(hipMalloc(&B->d_strips, sv.size() * sizeof(Tile)));
+    GG_HIP(dev_malloc((void **)&B->d_strips, sv.size() * sizeof(Tile)));
     GG_HIP(hipMemcpy(B->d_strips, sv.data(), sv.size() * sizeof(Tile), hipMemcpyHostToDevice));
   }
   if (!ss.empty()) {
-    GG_HIP(hipMalloc(&B->d_seg_strips, ss.size() * sizeof(Tile)));
+    GG_HIP(dev_malloc((void **)&B->d_seg_strips, ss.size() * sizeof(Tile)));
     GG_HIP(hipMemcpy(B->d_seg_strips, ss.data(), ss.size() * sizeof(Tile), hipMemcpyHostToDevice));
   }
   if (!B->side) {
