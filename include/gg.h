@@ -303,7 +303,9 @@ gg_status gg_set_launch(gg_lattice *lat, int32_t tile_x, int32_t tile_y,
  *     rows from LDS; the library picks the strips' height, and whether the
  *     strips that link to a segment run in the one kernel with the others
  *     (small lattices) or in a kernel of their own on the second stream.
- *     Other runs step as with fuse = 3 (strip_h 6 or 14). Lattices without
+ *     The smallest lattices (up to 1024 tiles) take their four steps over
+ *     tiles of 58 columns x 6 rows, all rows at once. Other runs, and mostly
+ *     the last four steps of a run, step as with fuse = 3 (strip_h 6 or 14). Lattices without
  *     pressure segments or the paper's walls, periodic axes of 4 nodes or
  *     more; otherwise fuse = 5 steps as fuse = 3. The
  *     result is that of single steps, bit for bit, as for every form.

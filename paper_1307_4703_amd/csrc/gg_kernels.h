@@ -41,6 +41,14 @@ hipError_t launch_tile2(gg_storage s, bool pairs, bool seg, int rows, const LatD
                         const Tile *tiles, int n_tiles, int dir, int dt, hipStream_t st,
                         bool press = false, void *tape0 = nullptr, void *tape1 = nullptr);
 
+// Four steps in one pass (t even, natural order in and out) over tiles of
+// TILE4_W columns x at most TILE4_H rows (flags >> 8), a work-group of TILE4_H +
+// 6 wavefronts each; seg: some tiles have their segment bit set; no pressure
+// segments; dir and dt as for launch_tile2.
+constexpr int TILE4_W = 58, TILE4_H = 6;
+hipError_t launch_tile4(gg_storage s, bool pairs, bool seg, const LatDesc *d, const Tile *tiles,
+                        int n_tiles, int dir, int dt, hipStream_t st);
+
 // ns steps in one pass (natural order in and out) through the kernel made
 // for max_steps, ns = 2..max_steps: one work-group of max_steps wavefronts
 // per strip of 64 - 2 (max_steps - 1) columns x (flags >> 8) rows, a

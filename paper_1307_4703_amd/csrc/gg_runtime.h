@@ -22,6 +22,7 @@ struct SegHost {
 struct PipePlan {
   int steps = 4, rows = 16;
   bool fork = false;
+  bool tiles = false;  // four-step tiles in place of strips (small lattices)
   int width() const { return 64 - 2 * (steps - 1); }
   int halo() const { return steps - 2; }  // build_pipe's
 };
@@ -32,6 +33,7 @@ struct PipeStrips {
   gg::Tile *d_main = nullptr, *d_seg = nullptr;
   int n_main = 0, n_seg = 0;
   int64_t main_fluid = 0, seg_fluid = 0;
+  bool tiles_seg = false;  // (plan.tiles) some tiles touch a segment
   bool none() const { return n_main + n_seg == 0; }
 };
 

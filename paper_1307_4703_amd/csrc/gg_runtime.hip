@@ -294,26 +294,28 @@ static void build_tiles(const gg_lattice *L, int tx, int ty, int inst,
 // to right: horizontally adjacent strips store into the same cache lines at
 // their common edge every row, so they go to the same XCD (a contiguous run
 // of the list) and run side by side in one work-group. Flags: strip height
-// << 8 | segment bit.
+// << 8 | segment bit. The four-step tiles are laid the same way, TILE4_W
+// columns wide.
 constexpr int STRIP_WIDTH = 62;
 // Does a strip hold a fluid node (any), one that links to a segment (sg).
-static void scan_strip(const gg_lattice *L, int x0, int y0, int rows, bool &any, bool &sg) {
+static void scan_strip(const gg_lattice *L, int x0, int y0, int width, int rows, bool &any,
+                       bool &sg) {
   any = sg = false;
   for (int y = y0; y < std::min(y0 + rows, L->ny); ++y)
-    for (int x = x0; x < std::min(x0 + STRIP_WIDTH, L->nx); ++x) {
+    for (int x = x0; x < std::min(x0 + width, L->nx); ++x) {
       if (L->link[L->nid(x, y)] == NOT_FLUID) continue;
       any = true;
       if (L->touches_seg[(size_t)y * L->nx + x]) sg = true;
     }
 }
 static void build_strips(const gg_lattice *L, int h, int inst, std::vector<Tile> &out,
-                         int halo = 0) {
-  const int width = STRIP_WIDTH;
+                         int halo = 0, int width = STRIP_WIDTH) {
   auto scan = [&](int x0, int y0, int rows, bool &any, bool &sg) {
-    scan_strip(L, x0, y0, rows, any, sg);
+    scan_strip(L, x0, y0, width, rows, any, sg);
     // halo 1 (pressure segments, rescaled at load): also when a node of
-    // the one-node halo the tile collides touches a segment (wrapped on
-    // periodic axes)
+    // the one-node halo the tile collides touches a segment; halo 2 (the
+    // four-step tiles): within two nodes of the tile, the nodes whose state
+    // at t + 1 the tile completes (wrapped on periodic axes)
     for (int yr = y0 - halo; halo > 0 && !sg && yr <= y0 + rows - 1 + halo; ++yr)
       for (int xr = x0 - halo; !sg && xr <= x0 + width - 1 + halo; ++xr) {
         int x = xr, y = yr;
@@ -363,9 +365,10 @@ static void build_strips(const gg_lattice *L, int h, int inst, std::vector<Tile>
 // The strips of build_strips (no halo) as two lists: one with links to a
 // segment is cut into 2-row strips, and those with such links go to the
 // second list, everything else to the first.
-static void split_strips(const gg_lattice *L, const std::vector<Tile> &all, std::vector<Tile> &main,
-                         std::vector<Tile> &seg) {
+static void split_strips(const gg_lattice *const *lats, const std::vector<Tile> &all,
+                         std::vector<Tile> &main, std::vector<Tile> &seg) {
   for (const Tile &t : all) {
+    const gg_lattice *L = lats[t.inst];
     if (!(t.flags & TILE_TOUCHES_SEGMENT)) {
       main.push_back(t);
       continue;
@@ -374,7 +377,7 @@ static void split_strips(const gg_lattice *L, const std::vector<Tile> &all, std:
     for (int y = t.y0; y < std::min(t.y0 + h, L->ny); y += 2) {
       const int rows = std::min(2, t.y0 + h - y);
       bool any, sg;
-      scan_strip(L, t.x0, y, rows, any, sg);
+      scan_strip(L, t.x0, y, STRIP_WIDTH, rows, any, sg);
       if (!any) continue;
       (sg ? seg : main).push_back(Tile{t.inst, t.x0, y, (rows << 8) | (sg ? TILE_TOUCHES_SEGMENT : 0)});
     }
@@ -607,6 +610,24 @@ static bool pass4_ok(const gg_lattice *L) {
          (!L->p.periodic_x || L->nx >= 4) && (!L->p.periodic_y || L->ny >= 4);
 }
 
+// Four-step tiles up to which the passes of four steps run over them
+// (launch_tile4) and not over pipelined strips: all rows of a tile step at
+// once, a strip's one after another, and while all tiles are on the GPU
+// together that is what a pass takes. Us for 64 steps, strips -> tiles: 128 x 64
+// channel (33 tiles) FP32 452 -> 228, FP64 485 -> 274; 333 x 215 periodic box
+// (216) FP32 248 -> 119, FP16 268 -> 119; gradient generator 1024 x 512 (399)
+// FP32 315 -> 283, FP64 391 -> 335; 600 x 500 all fluid (924) FP32 298 -> 230,
+// FP64 411 -> 417; 1000 x 500 (1512) FP32 339 -> 326, FP64 503 -> 598.
+static int tile4_tiles(gg_storage s) { return s == GG_F64 ? 768 : 1024; }
+static bool four_step_tiles(const gg_lattice *const *lats, int n, std::vector<Tile> &tiles) {
+  const int most = tile4_tiles(lats[0]->storage);
+  int64_t fluid = 0;
+  for (int k = 0; k < n; ++k) fluid += lats[k]->n_fluid;
+  if (fluid > (int64_t)most * TILE4_W * TILE4_H) return false;
+  for (int k = 0; k < n; ++k) build_strips(lats[k], TILE4_H, k, tiles, 2, TILE4_W);
+  return (int)tiles.size() <= most;
+}
+
 // The strips of the pipelined passes over the n lattices (n = 0: none) into
 // lists[0..1], in device memory of `owner`'s allocator (null: hipMalloc).
 static gg_status pipe_strips(const gg_lattice *const *lats, int n, const gg_lattice *owner,
@@ -621,9 +642,17 @@ static gg_status pipe_strips(const gg_lattice *const *lats, int n, const gg_latt
   for (int i = 0; i < 2 && n > 0; ++i) {
     if (i == 1 && lists[0].plan.steps <= 4) break;
     PipeStrips &p = lists[i];
-    p.plan = pipe_plan(lats, n, i == 0 ? 8 : 4);
     std::vector<Tile> main, seg;
-    for (int k = 0; k < n; ++k) {
+    p.plan.tiles = i == 0 && four_step_tiles(lats, n, main);
+    if (p.plan.tiles) {
+      p.plan.rows = TILE4_H;
+      for (const Tile &t : main) p.tiles_seg = p.tiles_seg || (t.flags & TILE_TOUCHES_SEGMENT) != 0;
+      for (int k = 0; k < n; ++k) p.main_fluid += lats[k]->n_fluid;
+    } else {
+      main.clear();
+      p.plan = pipe_plan(lats, n, i == 0 ? 8 : 4);
+    }
+    for (int k = 0; k < n && !p.plan.tiles; ++k) {
       const size_t m0 = main.size(), s0 = seg.size();
       build_pipe(lats[k], p.plan.rows, k, p.plan.width(), p.plan.halo(), main, seg);
       p.main_fluid += owned_fluid(lats[k], main, p.plan.width(), m0);
@@ -643,11 +672,14 @@ static gg_status pipe_strips(const gg_lattice *const *lats, int n, const gg_latt
   return GG_OK;
 }
 
-// One pipelined pass of `steps` steps over the strips p: the segment strips in
-// the one kernel with the others or, forked and joined, beside them.
+// One pass of `steps` steps over the strips p: over four-step tiles (steps 4),
+// or pipelined, the segment strips in the one kernel with the others or, forked
+// and joined, beside them.
 static hipError_t launch_strips(gg_storage storage, bool pairs, const LatDesc *d,
                                 const PipeStrips &p, int dir, int dt, int steps, hipStream_t st,
                                 hipStream_t side, hipEvent_t ev_fork, hipEvent_t ev_join) {
+  if (p.plan.tiles)
+    return launch_tile4(storage, pairs, p.tiles_seg, d, p.d_main, p.n_main, dir, dt, st);
   auto run = [&](const Tile *sl, int ns, const Tile *ml, int nm, hipStream_t q) {
     return launch_pipe(storage, pairs, p.plan.steps, d, sl, ns, ml, nm, dir, dt, steps, q);
   };
@@ -662,9 +694,9 @@ static hipError_t launch_strips(gg_storage storage, bool pairs, const LatDesc *d
   return e;
 }
 
-// n steps (a multiple of four, from an even step) in pairs of pipelined passes
-// (which end in the first plane set), the last ones of fewer steps:
-// launch(strips, dir, dt, steps) launches one.
+// n steps (a multiple of four, from an even step) in pairs of passes (which end
+// in the first plane set), the last ones of fewer steps: launch(strips, dir, dt,
+// steps) launches one.
 template <class F>
 static hipError_t launch_pipes(const PipeStrips *lists, int64_t n, F &&launch) {
   hipError_t e = hipSuccess;
@@ -687,6 +719,19 @@ static hipError_t launch_pipes(const PipeStrips *lists, int64_t n, F &&launch) {
 // tiles) 278 and 1852 -> 239 and 1810, but FP16 168 and 968 -> 151 and 1085.
 constexpr int ONE_KERNEL_TILES = 3072;
 
+// Does the pair of two-step passes that ends a run of fuse 5 go over pipelined
+// strips: where two-step tiles would need the boundary kernel apart (apart), up
+// to this many fluid nodes; its launch, fork and join cost more there than the
+// pipeline's wider halo. Us for four steps, tiles (in one kernel, or apart where
+// noted) and pipeline: 1000 x 500 all fluid FP32 35 and 44, 2200 x 1400 168 and
+// 194; gradient generator 1024 x 512 FP32 29 and 35, 3000 x 1500 (1.0M) apart 95
+// and 70, FP16 88 and 65, FP64 149 and 144; ten of 1536 x 768 (2.3M), apart, FP32
+// 192 and 184, FP16 131 and 144, FP64 342 and 385.
+constexpr int64_t PIPE2_NODES = 1500000;
+static bool pipe_pairs(const PipeStrips &p, bool apart, int64_t n_fluid) {
+  return !p.plan.tiles && apart && n_fluid <= PIPE2_NODES;
+}
+
 // A call that fails on the way leaves no list behind (and no graph that holds
 // one); the next step builds them again (lists_ready).
 gg_status gg_rebuild_tiles(gg_lattice *L) {
@@ -705,9 +750,10 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
     GG_HIP(hipMemcpy(L->d_tiles, t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice));
   }
   L->n_tiles = (int)t.size();
+  const gg_lattice *self[1] = {L};
   // the two-step pass's tiles: whole, for the one-kernel form (fuse 4, and
-  // fuse 3 on small lattices without pressure segments), and split, for the
-  // form with the boundary tiles apart, in one buffer
+  // fuse 3 and 5 on small lattices without pressure segments), and split, for
+  // the form with the boundary tiles apart, in one buffer
   std::vector<Tile> all, main, seg;
   // with pressure segments the one-kernel pass rescales the state it loads
   // in every tile that collides a boundary node, halo included
@@ -716,8 +762,8 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
   L->whole_seg = L->fuse == 4;
   for (const Tile &tl : all) L->whole_seg = L->whole_seg || (tl.flags & TILE_TOUCHES_SEGMENT) != 0;
   if (L->fuse != 4) {
-    split_strips(L, all, main, seg);
-    if (L->fuse != 3 || (int)all.size() > ONE_KERNEL_TILES) all.clear();
+    split_strips(self, all, main, seg);
+    if ((L->fuse != 3 && L->fuse != 5) || (int)all.size() > ONE_KERNEL_TILES) all.clear();
   }
   if (L->d_pass_tiles) (void)dev_free(L, L->d_pass_tiles);
   L->d_pass_tiles = L->d_whole = L->d_strips = L->d_seg_strips = nullptr;
@@ -739,7 +785,6 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
   L->n_seg_strips = (int)seg.size();
   // the pipelined passes' strips
   L->tiles4 = pass4_ok(L);
-  const gg_lattice *self[1] = {L};
   const gg_status st = pipe_strips(self, L->tiles4 ? 1 : 0, L, L->pipe);
   if (st != GG_OK) return st;
   L->lists_ok = true;
@@ -1316,7 +1361,7 @@ static hipError_t prof_end(gg_lattice *L, hipStream_t st, long idx, int kind) {
 }
 
 // The two-step pass takes all tiles in one kernel (with pressure segments only
-// as fuse 4: fuse 3 keeps the boundary kernel apart).
+// as fuse 4: fuse 3 and 5 keep the boundary kernel apart).
 static bool one_kernel(const gg_lattice *L) {
   return L->n_whole > 0 && (L->fuse == 4 || !has_pressure(L));
 }
@@ -1361,7 +1406,9 @@ static hipError_t launch_pass(gg_lattice *L, int dir, int dt, hipStream_t st) {
 static hipError_t launch_steps(gg_lattice *L, int64_t t0, int64_t n, hipStream_t st) {
   hipError_t e = hipSuccess;
   if (L->tiles4 && pass4_ok(L) && !(t0 & 1) && n % 4 == 0) {
+    const bool pairs = pipe_pairs(L->pipe[0], !one_kernel(L) && L->n_seg_strips > 0, L->n_fluid);
     e = launch_pipes(L->pipe, n, [&](const PipeStrips &p, int dir, int dt, int steps) {
+      if (steps == 2 && !pairs) return launch_pass(L, dir, dt, st);
       // (with the segment strips beside them, the pair of events spans both)
       long pidx = -1;
       hipError_t r = prof_begin(L, st, pidx);
@@ -2148,11 +2195,13 @@ struct gg_batch {
   std::vector<uint8_t> pop_b_created;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
-  // two-step pass over all members (fuse 3 or 4, tiles of `rows` rows);
-  // fuse 5: pipelined passes over the members' strips
+  // two-step pass over all members (tiles of `rows` rows), all tiles in one
+  // list and kernel (whole) or the boundary tiles apart; fuse 5: passes over
+  // `pipe` first
   int fuse = 1, rows = 6;
   Tile *d_strips = nullptr, *d_seg_strips = nullptr;
   int n_strips = 0, n_seg_strips = 0;
+  bool whole = false, whole_seg = false;
   PipeStrips pipe[2];
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -2211,13 +2260,13 @@ static hipError_t batch_launch(gg_batch *B, int64_t s0, int64_t n, hipStream_t s
       if (r == hipSuccess) r = hipStreamWaitEvent(st, B->ev_join, 0);
       return r;
     };
-    // (the boundary list holds 2-row tiles; fuse 4's one list, run with the
-    // boundary rules, holds tiles of `rows` rows)
+    // (the boundary list holds 2-row tiles; the one list of the one-kernel form
+    // tiles of `rows` rows)
     auto pass = [&](int dir, int dt) -> hipError_t {
       auto run = [&](bool seg, int rows, const Tile *list, int nl, hipStream_t q) {
         return launch_tile2(B->storage, B->pairs, seg, rows, B->d_descs, list, nl, dir, dt, q);
       };
-      if (B->fuse == 4) return run(true, B->rows, B->d_strips, B->n_strips, st);
+      if (B->whole) return run(B->whole_seg, B->rows, B->d_strips, B->n_strips, st);
       if (B->n_strips == 0) return run(true, 2, B->d_seg_strips, B->n_seg_strips, st);
       return apart(
           B->n_seg_strips > 0,
@@ -2225,7 +2274,9 @@ static hipError_t batch_launch(gg_batch *B, int64_t s0, int64_t n, hipStream_t s
           [&](hipStream_t q) { return run(false, B->rows, B->d_strips, B->n_strips, q); });
     };
     if (B->fuse == 5) {
+      const bool pairs = pipe_pairs(B->pipe[0], !B->whole && B->n_seg_strips > 0, B->n_fluid);
       e = launch_pipes(B->pipe, n, [&](const PipeStrips &p, int dir, int dt, int steps) {
+        if (steps == 2 && !pairs) return pass(dir, dt);
         return launch_strips(B->storage, B->pairs, B->d_descs, p, dir, dt, steps, st, B->side,
                              B->ev_fork, B->ev_join);
       });
@@ -2550,13 +2601,14 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
   B->rows = rows;
   if (fuse == 1) return GG_OK;
   std::vector<Tile> sv, ss;
-  for (size_t k = 0; k < B->lats.size() && fuse != 5; ++k) {
+  for (size_t k = 0; k < B->lats.size(); ++k) build_strips(B->lats[k], rows, (int)k, sv);
+  B->whole = fuse == 4 || (fuse == 5 && (int)sv.size() <= ONE_KERNEL_TILES);
+  B->whole_seg = fuse == 4;
+  for (const Tile &t : sv) B->whole_seg = B->whole_seg || (t.flags & TILE_TOUCHES_SEGMENT) != 0;
+  if (!B->whole) {
     std::vector<Tile> all;
-    build_strips(B->lats[k], rows, (int)k, all);
-    if (fuse == 4)
-      sv.insert(sv.end(), all.begin(), all.end());
-    else
-      split_strips(B->lats[k], all, sv, ss);
+    all.swap(sv);
+    split_strips(B->lats.data(), all, sv, ss);
   }
   if (!sv.empty()) {
     GG_HIP(dev_malloc((void **)&B->d_strips, sv.size() * sizeof(Tile)));
