@@ -555,7 +555,11 @@ static int pipe_pick_rows(int64_t strip_rows, int steps, int slots, int cus, boo
 // and 32.3). Inside the cache the longer pipeline fill costs more than the
 // trips save (the 2048 x 1024 gradient generator keeps 4). FP16 is bound by
 // its arithmetic with 4 already (143-150 us a step with 8, 145 with 4), and
-// FP64 has LDS for too few work-groups of 8 (or 6: 551 against 416).
+// FP64 has LDS for too few work-groups of 8 (or 6: 551 against 416). A batch
+// takes 8 where its members' planes no longer fit (64 steps: ten chips, 2.25M
+// nodes, 1921 us with 8 and 1584 with 4; twelve, 2.64M, 1685 and 1805), a
+// single lattice from PIPE8_NODES (all fluid 2.1M nodes 794 and 748, 2.4M 926
+// and 1110, gradient generator 2.4M 1199 and 1485).
 constexpr int64_t PIPE8_NODES = 2000000;
 static PipePlan pipe_plan(const gg_lattice *const *lats, int n, int max_steps) {
   PipePlan p;
@@ -568,8 +572,9 @@ static PipePlan pipe_plan(const gg_lattice *const *lats, int n, int max_steps) {
     for (bool b : lats[k]->seg_present) segments = segments || b;
   }
   const gg_storage st = lats[0]->storage;
-  if (max_steps >= 8 && st == GG_F32 && wrap8 && fluid >= PIPE8_NODES) p.steps = 8;
   const bool cached = fluid * 2 * NPOP * (int64_t)lats[0]->esize <= (int64_t)256 << 20;
+  if (max_steps >= 8 && st == GG_F32 && wrap8 && (n == 1 ? fluid >= PIPE8_NODES : !cached))
+    p.steps = 8;
   int64_t strip_rows = 0;
   for (int k = 0; k < n; ++k) strip_rows += pipe_strip_rows(lats[k], p.width());
   // segment strips in the one kernel while all work-groups fit at once or

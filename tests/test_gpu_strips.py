@@ -98,7 +98,7 @@ def test_eight_steps_and_their_fluxes(layout, chunk):
 
 
 @pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
-@pytest.mark.parametrize("size", [1, 4, 14])
+@pytest.mark.parametrize("size", [1, 4, 14, 16])
 def test_batches(storage, size):
     """Uneven members in tiles, in strips and, FP32, in passes of eight steps;
     the boundary tiles in the one kernel and apart."""
