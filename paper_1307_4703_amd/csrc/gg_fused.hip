@@ -23,7 +23,9 @@
 // so the result is the one the single-step kernels give. The halo lanes and
 // rows are collided for step t only, for the populations they send into
 // the strip; they are owned by the neighbouring strips, which collide and
-// store them themselves.
+// store them themselves. Strips with links to boundary segments go to the
+// row-parallel kernel below, two rows a tile: their walk would be the longest
+// of the pass (128 x 64 channel in FP32, 64 steps, strips of 8 rows: 1030 us walked, 569 so).
 #include "gg_device.h"
 #include "gg_kernels.h"
 #include "gg_node.h"
@@ -49,10 +51,9 @@ __device__ __forceinline__ void second_step(CDesc &L, const Planes<typename Pop<
   push_node<S>(L, dst, x, y, L.periodic_x || L.periodic_y, lc, qf, qg, jf, jg);
 }
 
-template <class S, bool SEG, bool PAIRS>
+template <class S, bool PAIRS>
 __device__ __forceinline__ void strip_two_steps(const LatDesc *__restrict__ descs,
-                                                const Tile *__restrict__ strips, int s, int dir,
-                                                int dt) {
+                                                const Tile *__restrict__ strips, int s, int dir) {
   using P = Pop<S>;
   using T = typename P::T;
   using W = typename P::W;
@@ -61,13 +62,7 @@ __device__ __forceinline__ void strip_two_steps(const LatDesc *__restrict__ desc
   CDesc &L = ((CDesc *)descs)[tl.inst];
   const int nx = L.nx, ny = L.ny, pitch = L.pitch;
   const int H = strip_rows(tl.flags);
-  const int64_t t = *(const GG_CONST int64_t *)L.t + dt;
-  PhaseNow ph1{0u, nullptr}, ph2{0u, nullptr};
-  if (SEG) {
-    const Phases<2> ph(L, t);
-    ph1 = ph.ph[0];
-    ph2 = ph.ph[1];
-  }
+  const PhaseNow ph{0u, nullptr};  // (no links to segments)
   const Planes<W> src(dir ? L.pop_b : L.pop, L.plane, PAIRS);  // (the lattice's layout)
   const Planes<W> dst(dir ? L.pop : L.pop_b, L.plane, PAIRS);
   const GG_GLOBAL uint8_t *link = (const GG_GLOBAL uint8_t *)L.link;
@@ -151,7 +146,7 @@ __device__ __forceinline__ void strip_two_steps(const LatDesc *__restrict__ desc
     // step t at (x, y)
     T pf[9], pg[5], inf[9], ing[5];
     if (lc != NOT_FLUID) {
-      collide_node<T, false, FluxT<T>>(L, x, y, lc, SEG, ph1, f, g, pf, pg, inf, ing, fx, own);
+      collide_node<T, false, FluxT<T>>(L, x, y, lc, false, ph, f, g, pf, pg, inf, ing, fx, own);
     } else {
 #pragma unroll
       for (int i = 0; i < 9; ++i) pf[i] = inf[i] = T(0);
@@ -164,16 +159,13 @@ __device__ __forceinline__ void strip_two_steps(const LatDesc *__restrict__ desc
     const T vf5 = from_left(pf[5]), vf6 = from_right(pf[6]);
     const T df7 = from_right(pf[7]), df8 = from_left(pf[8]);
 
-    // (each collision's fluxes leave on their own, as a single step's do;
-    // every lane of the wavefront takes part)
-    if (SEG) fx.flush((double *)L.flux);
     // the previous row pulls f4, f7, f8, g4 from this row: step t + 1 there
     if (own_prev && lcp != NOT_FLUID) {
       if (!src_solid(lcp, 4)) sf[4] = P::rt(pf[4]);
       if (!src_solid(lcp, 7)) sf[7] = P::rt(df7);
       if (!src_solid(lcp, 8)) sf[8] = P::rt(df8);
       if (!src_solid(lcp, 4)) sg[4] = P::rt(pg[4]);
-      second_step<S, SEG, false, FluxT<T>>(L, dst, x, yprev, lcp, ph2, sf, sg, fx);
+      second_step<S, false, false, FluxT<T>>(L, dst, x, yprev, lcp, ph, sf, sg, fx);
     }
 
     // state at t + 1 of this row, without the pulls from the row below
@@ -200,7 +192,6 @@ __device__ __forceinline__ void strip_two_steps(const LatDesc *__restrict__ desc
     lcp = lc;
     yprev = y;
     own_prev = own;
-    if (SEG) fx.flush((double *)L.flux);
   }
 }
 
@@ -209,19 +200,17 @@ __device__ __forceinline__ void strip_two_steps(const LatDesc *__restrict__ desc
 // wavefront. Work-groups are dealt to the 8 XCDs so that each XCD walks a
 // contiguous run of strips (the list runs along each band of rows, so
 // neighbouring strips, which share cache lines at their edges, share an L2).
-// SEG: strips with links to boundary segments (their own kernel, so that
-// the boundary rules do not set the register budget of the others).
-template <class S, bool SEG, bool PAIRS>
+template <class S, bool PAIRS>
 __global__ void __launch_bounds__(256)
     k_step2(const LatDesc *__restrict__ descs, const Tile *__restrict__ strips, int n_strips,
-            int per_xcd, int dir, int dt) {
+            int per_xcd, int dir) {
   const int nb = 8 * per_xcd;
   // the wavefront index, marked uniform so that the strip, the descriptor
   // and the plane bases are read with scalar loads
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   for (int b = blockIdx.x; b < nb; b += gridDim.x) {
     const int s = ((b & 7) * per_xcd + (b >> 3)) * 4 + w;
-    if (s < n_strips) strip_two_steps<S, SEG, PAIRS>(descs, strips, s, dir, dt);
+    if (s < n_strips) strip_two_steps<S, PAIRS>(descs, strips, s, dir);
   }
 }
 
@@ -630,20 +619,20 @@ __global__ void __launch_bounds__((R + 6) * 64)
 
 }  // namespace
 
-hipError_t launch_step2(gg_storage s, bool pairs, bool seg, const LatDesc *d, const Tile *strips,
-                        int n_strips, int dir, int dt, hipStream_t st, int persist) {
+hipError_t launch_step2(gg_storage s, bool pairs, const LatDesc *d, const Tile *strips,
+                        int n_strips, int dir, hipStream_t st, int persist) {
   if (n_strips <= 0) return hipSuccess;
   const int nblk = (n_strips + 3) / 4;
   const int per_xcd = (nblk + 7) / 8;
   int grid = 8 * per_xcd;
   if (persist > 0) grid = std::min(grid, (persist + 7) / 8 * 8);
-#define GG_LAUNCH2(TYPE, SEGV)                                                              \
-  (pairs ? k_step2<TYPE, SEGV, true><<<grid, 256, 0, st>>>(d, strips, n_strips, per_xcd, dir, dt) \
-         : k_step2<TYPE, SEGV, false><<<grid, 256, 0, st>>>(d, strips, n_strips, per_xcd, dir, dt))
+#define GG_LAUNCH2(TYPE)                                                                   \
+  (pairs ? k_step2<TYPE, true><<<grid, 256, 0, st>>>(d, strips, n_strips, per_xcd, dir)    \
+         : k_step2<TYPE, false><<<grid, 256, 0, st>>>(d, strips, n_strips, per_xcd, dir))
   switch (s) {
-    case GG_F64: if (seg) GG_LAUNCH2(double, true); else GG_LAUNCH2(double, false); break;
-    case GG_F32: if (seg) GG_LAUNCH2(float, true); else GG_LAUNCH2(float, false); break;
-    case GG_F16_SHIFTED: if (seg) GG_LAUNCH2(__half, true); else GG_LAUNCH2(__half, false); break;
+    case GG_F64: GG_LAUNCH2(double); break;
+    case GG_F32: GG_LAUNCH2(float); break;
+    case GG_F16_SHIFTED: GG_LAUNCH2(__half); break;
   }
 #undef GG_LAUNCH2
   return hipGetLastError();

@@ -21,11 +21,10 @@ hipError_t launch_step_tape(gg_storage s, bool pairs, int block, bool odd, const
                             hipStream_t st);
 
 // Two steps in one pass (t even, natural order in): strips of 62 columns x
-// (flags >> 8) rows, four per 256-thread work-group; seg selects the kernel
-// for strips with segment links; dir 0 reads the plane set pop and writes
-// pop_b, dir 1 the reverse; dt as for launch_step.
-hipError_t launch_step2(gg_storage s, bool pairs, bool seg, const LatDesc *d, const Tile *strips,
-                        int n_strips, int dir, int dt, hipStream_t st, int persist = 0);
+// (flags >> 8) rows without links to segments, four per 256-thread work-group;
+// dir 0 reads the plane set pop and writes pop_b, dir 1 the reverse.
+hipError_t launch_step2(gg_storage s, bool pairs, const LatDesc *d, const Tile *strips,
+                        int n_strips, int dir, hipStream_t st, int persist = 0);
 
 // The same two steps row-parallel: one work-group of rows + 2 wavefronts
 // per tile of 62 columns x (flags >> 8) rows, rows 2, 6 or 14; seg selects

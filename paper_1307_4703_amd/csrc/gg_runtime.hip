@@ -1389,9 +1389,9 @@ static hipError_t launch_pass(gg_lattice *L, int dir, int dt, hipStream_t st) {
   }
   auto run = [&](bool seg, const Tile *list, int n, hipStream_t s) {
     // the segment list holds 2-row tiles
-    return L->fuse >= 3 ? launch_tile2(L->storage, L->pairs, seg, seg ? 2 : L->strip_h, L->d_desc,
-                                       list, n, dir, dt, s, press)
-                        : launch_step2(L->storage, L->pairs, seg, L->d_desc, list, n, dir, dt, s);
+    return seg || L->fuse >= 3
+               ? launch_tile2(L->storage, L->pairs, seg, seg ? 2 : L->strip_h, L->d_desc, list, n, dir, dt, s, press)
+               : launch_step2(L->storage, L->pairs, L->d_desc, list, n, dir, s);
   };
   if (fork) {
     e = hipEventRecord(L->ev_fork, st);
