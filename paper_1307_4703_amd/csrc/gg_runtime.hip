@@ -714,15 +714,19 @@ static hipError_t launch_pipes(const PipeStrips *lists, int64_t n, F &&launch) {
   return e;
 }
 
-// Tiles up to which fuse 3 takes the boundary tiles in the one kernel with the
-// others: up to about a round of them (the boundary kernel holds 12 of its
-// wavefronts of 6-row tiles a CU), a second kernel's launch, fork and join cost
-// more than the registers of the boundary rules. Us for 8 steps launched one by
-// one and for 64 from a graph, two kernels -> one, FP32: 128 x 64 channel 140
-// and 512 -> 57 and 369, gradient generator 410 x 205 130 and 428 -> 42 and
-// 253, 2048 x 1024 (1300 tiles) 140 and 558 -> 79 and 540, 4096 x 2048 (5200
-// tiles) 278 and 1852 -> 239 and 1810, but FP16 168 and 968 -> 151 and 1085.
-constexpr int ONE_KERNEL_TILES = 3072;
+// Tiles up to which fuse 3 and 5 take the boundary tiles in the one kernel with
+// the others. A second kernel's launch, fork and join cost 45 us for four steps
+// launched one by one, 5 a pass from a graph; the registers of the boundary
+// rules cost a share of every tile, the most where the kernel without them is
+// short (FP16) or holds twice the work-groups (14 rows in FP16 and FP32). Us for
+// 64 steps from a graph, two kernels and one: 6 rows, gradient generator 1024 x
+// 512 (365 tiles) FP32 419 and 272, 2500 x 1250 (1976) FP32 693 and 660, FP16 562
+// and 578, 3000 x 1500 (3140) FP32 917 and 841, FP16 693 and 714, FP64 1892 and
+// 1899, 4096 x 2048 (5726) FP32 1872 and 1788, FP16 1024 and 1093; 14 rows, 1400
+// x 700 (358) FP32 461 and 406, FP16 427 and 395, 2048 x 1024 (630) FP32 612 and
+// 630, FP16 513 and 535, 2500 x 1250 (844) FP32 745 and 787, FP16 599 and 693,
+// FP64 1242 and 1126. (Four steps one by one, 2500 x 1250 FP32: 91 and 53.)
+static int one_kernel_tiles(gg_storage s, int rows) { return rows > 6 && s != GG_F64 ? 512 : 3072; }
 
 // Does the pair of two-step passes that ends a run of fuse 5 go over pipelined
 // strips: where two-step tiles would need the boundary kernel apart (apart), up
@@ -768,7 +772,8 @@ gg_status gg_rebuild_tiles(gg_lattice *L) {
   for (const Tile &tl : all) L->whole_seg = L->whole_seg || (tl.flags & TILE_TOUCHES_SEGMENT) != 0;
   if (L->fuse != 4) {
     split_strips(self, all, main, seg);
-    if ((L->fuse != 3 && L->fuse != 5) || (int)all.size() > ONE_KERNEL_TILES) all.clear();
+    if ((L->fuse != 3 && L->fuse != 5) || (int)all.size() > one_kernel_tiles(L->storage, L->strip_h))
+      all.clear();
   }
   if (L->d_pass_tiles) (void)dev_free(L, L->d_pass_tiles);
   L->d_pass_tiles = L->d_whole = L->d_strips = L->d_seg_strips = nullptr;
@@ -2607,7 +2612,7 @@ gg_status gg_batch_set_two_step(gg_batch *B, int32_t fuse, int32_t rows) {
   if (fuse == 1) return GG_OK;
   std::vector<Tile> sv, ss;
   for (size_t k = 0; k < B->lats.size(); ++k) build_strips(B->lats[k], rows, (int)k, sv);
-  B->whole = fuse == 4 || (fuse == 5 && (int)sv.size() <= ONE_KERNEL_TILES);
+  B->whole = fuse == 4 || (fuse == 5 && (int)sv.size() <= one_kernel_tiles(B->storage, rows));
   B->whole_seg = fuse == 4;
   for (const Tile &t : sv) B->whole_seg = B->whole_seg || (t.flags & TILE_TOUCHES_SEGMENT) != 0;
   if (!B->whole) {
