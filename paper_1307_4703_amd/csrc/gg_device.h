@@ -262,25 +262,28 @@ template <> struct Pop<__half> {
   // the value a store followed by a load gives back
   static __device__ __forceinline__ T rt(T v) { return __half2float(to_half(v)); }
   // Two values rounded by one packed conversion (v_cvt_pk_f16_f32: round to
-  // nearest even, as the single conversion), behind the same barrier: where
-  // the two halves are used apart the compiler takes the conversion apart
-  // again and folds it like the single one.
+  // nearest even, as the single conversion). Where the two halves are used
+  // apart (rt2, st2) the compiler may take the conversion apart again and fold
+  // it like the single one, so these stand behind the same barrier; a packed
+  // result that is stored whole stays a packed conversion (a barrier there too
+  // costs the FP16 passes 3 %). The tests look for folded ones in the library.
   using H2 = _Float16 __attribute__((ext_vector_type(2)));
   using F2 = float __attribute__((ext_vector_type(2)));
   static __device__ __forceinline__ H2 to_half2(T a, T b) {
-    asm("" : "+v"(a), "+v"(b));
     F2 v;
     v[0] = a;
     v[1] = b;
     return __builtin_convertvector(v, H2);
   }
   static __device__ __forceinline__ void st2(GG_GLOBAL W *p, GG_GLOBAL W *q, T a, T b) {
+    asm("" : "+v"(a), "+v"(b));
     const H2 h = to_half2(a, b);
     const _Float16 h0 = h[0], h1 = h[1];
     gstore(p, __builtin_bit_cast(W, h0));
     gstore(q, __builtin_bit_cast(W, h1));
   }
   static __device__ __forceinline__ void rt2(T &a, T &b) {
+    asm("" : "+v"(a), "+v"(b));
     const H2 h = to_half2(a, b);
     a = (T)h[0];
     b = (T)h[1];
