@@ -223,9 +223,8 @@ __device__ __forceinline__ void gather(CDesc &L, uint32_t node, uint8_t lc, int 
 // and 0 where there is no fluid; or (tiles) the fluid cells of a tile list alone.
 // One kernel over all cells writes each output once: four fields of a 2048 x
 // 1024 chip take 17.4 us, with a fill of each output before 37; a 128 x 64
-// one's 3.8, and 4.6 with four launches before it. On large lattices that are
-// mostly walls the fills are faster at theirs (8192 x 4096, a quarter fluid:
-// 286 us, 347 in one kernel; all fluid 528).
+// one's 3.8, and 4.6 with four launches before it. (Large lattices that are
+// mostly walls: see the runtime.)
 // ---------------------------------------------------------------------------
 template <class S>
 __global__ void __launch_bounds__(256)
@@ -247,40 +246,42 @@ __global__ void __launch_bounds__(256)
   const uint8_t lc = ((const GG_GLOBAL uint8_t *)L.link)[node];
   const int64_t n = (int64_t)L.nx * L.ny;
   const int64_t k = (int64_t)y * L.nx + x;
-  if (lc == NOT_FLUID) {
-    if (tiles) return;
-    const double none = __builtin_nan("");
-    if (rho_out) __builtin_nontemporal_store(none, &rho_out[k]);
-    if (ux_out) __builtin_nontemporal_store(none, &ux_out[k]);
-    if (uy_out) __builtin_nontemporal_store(none, &uy_out[k]);
-    if (c_out) __builtin_nontemporal_store(none, &c_out[k]);
-    if (f_out)
-      for (int i = 0; i < 9; ++i) __builtin_nontemporal_store(0.0, &f_out[i * n + k]);
-    if (g_out)
-      for (int i = 0; i < 5; ++i) __builtin_nontemporal_store(0.0, &g_out[i * n + k]);
-    return;
+  const bool fluid = lc != NOT_FLUID;
+  if (tiles && !fluid) return;
+  double f[9] = {}, g[5] = {};  // deviations, FP64
+  if (fluid) {
+    T fT[9], gT[5];
+    gather<S>(L, node, lc, x, y, fT, gT);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) f[i] = (double)fT[i];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) g[i] = (double)gT[i];
   }
-  T fT[9], gT[5];
-  gather<S>(L, node, lc, x, y, fT, gT);
-  double f[9], g[5];  // deviations, FP64
-  for (int i = 0; i < 9; ++i) f[i] = (double)fT[i];
-  for (int i = 0; i < 5; ++i) g[i] = (double)gT[i];
+  // one store an output for fluid and other cells together: a cache line with
+  // both is written once (a random mask's populations, 2048 x 1024: 162 us with
+  // the outputs filled first, 225 with a store for each kind, 90 so)
+  auto put = [&](double *out, int64_t at, double v, double none) {
+    __builtin_nontemporal_store(fluid ? v : none, &out[at]);
+  };
   if (f_out)
-    for (int i = 0; i < 9; ++i) __builtin_nontemporal_store(f[i] + WF[i] * L.rho0, &f_out[i * n + k]);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) put(f_out, i * n + k, f[i] + WF[i] * L.rho0, 0.0);
   if (g_out)
+#pragma unroll
     for (int i = 0; i < 5; ++i) {
       // the weights of the step, in its compute type
       const T wga = (T)L.wg_axis;
       const double w = (double)(i == 0 ? T(1) - T(4) * wga : wga);
-      __builtin_nontemporal_store(g[i] + w * L.c_shift, &g_out[i * n + k]);
+      put(g_out, i * n + k, g[i] + w * L.c_shift, 0.0);
     }
+  const double none = __builtin_nan("");
   const double rho = L.rho0 + (f[0] + f[1] + f[2] + f[3] + f[4] + f[5] + f[6] + f[7] + f[8]);
   const double jx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]);
   const double jy = (f[2] - f[4]) + (f[5] - f[7]) + (f[6] - f[8]);
-  if (rho_out) __builtin_nontemporal_store(rho, &rho_out[k]);
-  if (ux_out) __builtin_nontemporal_store(jx / rho, &ux_out[k]);
-  if (uy_out) __builtin_nontemporal_store(jy / rho, &uy_out[k]);
-  if (c_out) __builtin_nontemporal_store(L.c_shift + (g[0] + g[1] + g[2] + g[3] + g[4]), &c_out[k]);
+  if (rho_out) put(rho_out, k, rho, none);
+  if (ux_out) put(ux_out, k, jx / rho, none);
+  if (uy_out) put(uy_out, k, jy / rho, none);
+  if (c_out) put(c_out, k, L.c_shift + (g[0] + g[1] + g[2] + g[3] + g[4]), none);
 }
 
 // Fills n doubles with a value.

@@ -1673,10 +1673,19 @@ static gg_status gg_read_impl(gg_lattice *L, double *rho, double *ux, double *uy
   const int64_t len[6] = {n, n, n, n, 9 * n, 5 * n};
   const double fillv[6] = {NAN, NAN, NAN, NAN, 0.0, 0.0};
   double *dev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  // mostly walls, and outputs beyond the Infinity Cache (256 MB): filled first
-  int64_t cells = 0;
-  for (int q = 0; q < 6; ++q) cells += user[q] ? len[q] : 0;
-  const bool fill = cells > ((int64_t)32 << 20) && 2 * L->n_fluid < n;
+  // Large lattices that are mostly walls have their outputs filled first and
+  // then the fluid's tiles read: a fill runs at 6 TB/s, the kernel over all cells
+  // waits for each cell's link code. Not where it writes a few outputs of a
+  // middling lattice, for which it saves their fills. (us for one field, two,
+  // four, and all populations, a quarter fluid, FP16, all cells and filled: 3000
+  // x 1500 38 and 36, 40 and 45, 44 and 63, 114 and 138; 4096 x 2048 64 and 47,
+  // 68 and 60, 74 and 94, 182 and 220, in FP64 86 and 67, 103 and 89, 132 and
+  // 144, 285 and 271; 5500 x 2750 74 and 67, 82 and 98, 136 and 162, 524 and
+  // 417; 8192 x 4096 255 and 142, 301 and 201, 402 and 302, 945 and 836.)
+  int64_t planes = 0;
+  for (int q = 0; q < 6; ++q) planes += user[q] ? len[q] / n : 0;
+  const bool fill = 2 * L->n_fluid < n && (n > ((int64_t)16 << 20) ||
+                    (n >= ((int64_t)8 << 20) && (planes <= 2 || planes > 5)));
   gg_status st = GG_OK;
   for (int q = 0; q < 6; ++q) {
     if (!user[q]) continue;
