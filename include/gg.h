@@ -386,12 +386,14 @@ gg_status gg_set_phase_fields(gg_lattice *lat, const int32_t *slots, int32_t n);
 gg_status gg_cde_step(gg_lattice *lat, int64_t n);
 
 /* Launch form of gg_cde_step: rows = 14 (the default), 6, -6 or -10 runs pairs
- * of passes of eight steps, then of four and of two, each of which reads the
- * compound state and the field once and writes the state that many steps
- * later into the second plane set (the compound planes only): one wavefront
- * per strip of 50 columns, the strips' rows chosen by the library. Lattices
- * with pressure segments run two-step passes over tiles of 14 rows (rows =
- * 14) or 6 rows (the others). rows = 0 keeps to single steps. GG_ERR_ARG for
+ * of passes, each of which reads the compound state and the field once and
+ * writes the state some steps later into the second plane set (the compound
+ * planes only). The library picks them: passes of eight steps, then of four, by
+ * one wavefront per strip of 50 columns; passes of four steps over tiles of 58
+ * columns x 6 rows (-rows with rows < 0) on small lattices, with a source and
+ * where the phases' fields change every few steps; passes of two steps over
+ * tiles of 14 rows (rows = 14) or 6 rows (the others) for what is left of a run
+ * and with pressure segments. rows = 0 keeps to single steps. GG_ERR_ARG for
  * other values. Every form gives the single steps' result bit for bit. */
 gg_status gg_set_cde_launch(gg_lattice *lat, int32_t rows);
 

@@ -66,12 +66,19 @@ int pipe_slots(gg_storage s, bool pairs, int max_steps, bool seg, int *cus);
 // step, dt as for launch_step.
 hipError_t launch_cde(gg_storage s, bool pairs, bool odd, const LatDesc *d, const Tile *tiles,
                       int n_tiles, int tx_shift, int dt, hipStream_t st);
-// Two compound-only steps in one pass on a lattice with pressure segments (t
-// even, natural order in; launch_rescale after it): one work-group of rows +
-// 2 wavefronts per tile of 62 columns x (flags >> 8) rows, rows 6 or 14; dir 0
-// reads the compound planes of pop and writes those of pop_b, dir 1 the
-// reverse, bit 1: rescale the state as loaded; dt as for launch_step.
+// Two compound-only steps in one pass (t even, natural order in): one
+// work-group of rows + 2 wavefronts per tile of 62 columns x (flags >> 8) rows,
+// rows 6 or 14; dir 0 reads the compound planes of pop and writes those of
+// pop_b, dir 1 the reverse; dt as for launch_step; press: the lattice has
+// pressure segments (launch_rescale after the pass; dir bit 1: rescale the
+// state as loaded).
 hipError_t launch_cde_tile2(gg_storage s, bool pairs, int rows, const LatDesc *d,
+                            const Tile *tiles, int n_tiles, int dir, int dt, hipStream_t st,
+                            bool press);
+// Four compound-only steps per pass (t even, no pressure segments): one
+// work-group of rows + 6 wavefronts per tile of TILE4_W columns x (flags >> 8)
+// rows, rows 6 or 10; dir and dt as for launch_tile2.
+hipError_t launch_cde_tile4(gg_storage s, bool pairs, int rows, const LatDesc *d,
                             const Tile *tiles, int n_tiles, int dir, int dt, hipStream_t st);
 // Compound-only passes of `steps` (2, 4 or 8) steps (t even, no pressure
 // segments): one wavefront per strip of CDE_WALK_W columns x (flags >> 8)

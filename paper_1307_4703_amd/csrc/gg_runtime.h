@@ -37,6 +37,9 @@ struct PipeStrips {
   bool none() const { return n_main + n_seg == 0; }
 };
 
+// Passes of the compound alone beside the two-step tiles.
+enum class CdeForm { tiles2, tiles4, walk };
+
 struct gg_lattice {
   gg_alloc alloc{};         // the caller's device allocator (has_alloc)
   bool has_alloc = false;
@@ -132,13 +135,14 @@ struct gg_lattice {
   int n_ufield = 0;
   uint32_t ufield_set = 0;
   int8_t phase_field[GG_MAX_PHASES] = {};
-  // compound-only steps (cde_rows 0: single steps): walking strips, with
-  // pressure segments two-step passes over tiles of cde_rows rows (6 with
-  // cde_rows < 0); the lists are built on first use
+  // compound-only steps (cde_rows 0: single steps): two-step tiles of cde_rows
+  // rows (6 with cde_rows < 0), four-step tiles of -cde_rows rows, walking
+  // strips; the lists of the form in force are built on first use
   int cde_rows = 14;
-  gg::Tile *d_cde_tiles = nullptr;
+  CdeForm cde_form = CdeForm::tiles2;
+  gg::Tile *d_cde_tiles = nullptr, *d_cde_tiles4 = nullptr;
   PipeStrips cde_walk;
-  int n_cde_tiles = 0, cde_tiles_rows = 0;
+  int n_cde_tiles = 0, n_cde_tiles4 = 0, cde_tiles_rows = 0;
   // buffers of the last adjoint run and their sizes, kept for the next (in
   // the runtime's KeptBuffers, whose lock guards them)
   std::vector<std::pair<void *, size_t>> adjoint_kept;

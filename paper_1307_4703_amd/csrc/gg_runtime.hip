@@ -174,7 +174,7 @@ void gg_free_device(gg_lattice *L) {
                   L->d_flux, L->d_acc, L->d_desc, L->d_tiles, L->d_aux_tiles,
                   L->d_pass_tiles, L->pipe[0].d_main, L->pipe[0].d_seg, L->pipe[1].d_main,
                   L->pipe[1].d_seg, L->d_partial, L->d_ufield,
-                  L->d_cde_tiles, L->cde_walk.d_main, L->cde_walk.d_seg,
+                  L->d_cde_tiles, L->d_cde_tiles4, L->cde_walk.d_main, L->cde_walk.d_seg,
                   L->d_press, L->d_wall, L->d_wall_links, L->d_wall_save,
                   L->d_mon};
   for (void *p : ptrs)
@@ -2893,16 +2893,57 @@ static int cde_walk_rows(int64_t strip_rows, int steps, int simds) {
   return best;
 }
 
-// Work lists of the compound-only passes: strips of the walk or, with pressure
-// segments, tiles of the two-step pass.
+// The form of the compound-only passes beside the two-step tiles (which do the
+// pairs of steps that end a run, and everything with pressure segments or on
+// periodic axes that a longer pass's halo would wrap twice). Us for 64 steps
+// unless noted, planes layout.
+//  - The walk takes its rows one after another, so small lattices go over
+//    four-step tiles, all rows at once: 128 x 64 channel FP32 248 walked, 127 in
+//    tiles, gradient generator 410 x 205 (19000 nodes) 157 and 139, 333 x 215 box
+//    (61000) 106 and 93, 1024 x 512 gradient generator (120000) 161 and 165, all
+//    fluid 1000 x 500 172 and 221.
+//  - A source, or a schedule whose field changes every few steps, puts every
+//    strip on the walk's general body, which costs it half its speed: 410 x 205
+//    with a source FP32 239 walked and 145 in tiles, 2048 x 1024 465 and 315, all
+//    fluid 2200 x 1400 1942 and 1087; phases of 4 steps and a field each, 2048 x
+//    1024, 1.45 times the tiles' time, of 12 steps 0.86, of 40 0.59. Large FP64
+//    lattices are bound by their trips through memory all the same (5500 x 2750
+//    gradient generator with a source, paired: 2469 and 3263), and large ones of
+//    the narrower types in planes by the tiles' halo: two-step tiles (all fluid
+//    4000 x 2000 FP16 2770 in four-step and 2152 in two-step tiles).
+constexpr int64_t CDE_TILES_NODES = 100000, CDE_PHASE = 12, CDE_LARGE = 3000000,
+                  CDE_LARGE_PLANES = 2000000;
+static CdeForm cde_form(const gg_lattice *L) {
+  const int axis = std::min(L->p.periodic_x ? L->nx : 8, L->p.periodic_y ? L->ny : 8);
+  if (has_pressure(L) || axis < 4) return CdeForm::tiles2;
+  bool general = L->d_R != nullptr;
+  for (size_t k = 0, n = L->phases.size(); k < n; ++k)
+    general = general || (L->phases[k].duration < CDE_PHASE &&
+                          L->phase_field[k] != L->phase_field[(k + 1) % n]);
+  if (!general) return L->n_fluid <= CDE_TILES_NODES ? CdeForm::tiles4 : CdeForm::walk;
+  if (L->storage == GG_F64) return L->n_fluid >= CDE_LARGE ? CdeForm::walk : CdeForm::tiles4;
+  return !L->pairs && L->n_fluid >= CDE_LARGE_PLANES && L->cde_rows > 0 ? CdeForm::tiles2
+                                                                        : CdeForm::tiles4;
+}
+
+// Rows of the four-step tiles.
+static int cde_rows4(const gg_lattice *L) { return L->cde_rows < 0 ? -L->cde_rows : 6; }
+
+// Work lists of the compound-only passes for the row count and form in force:
+// two-step tiles and, by the form, four-step tiles (in eight vertical stripes,
+// each walked band by band: an XCD takes a contiguous run of the list) or the
+// walk's strips.
 static gg_status cde_tiles(gg_lattice *L) {
-  if (L->cde_rows == 0 || L->cde_tiles_rows == L->cde_rows) return GG_OK;
-  if (L->d_cde_tiles) GG_HIP(dev_free(L, L->d_cde_tiles));
-  L->d_cde_tiles = nullptr;
-  L->n_cde_tiles = L->cde_tiles_rows = 0;
+  const CdeForm form = cde_form(L);
+  if (L->cde_rows == 0 || (L->cde_tiles_rows == L->cde_rows && L->cde_form == form)) return GG_OK;
+  gg_drop_cde_graphs(L);
+  L->n_cde_tiles = L->n_cde_tiles4 = L->cde_tiles_rows = 0;
   PipeStrips &w = L->cde_walk;
-  for (Tile *d : {w.d_main, w.d_seg})
-    if (d) GG_HIP(dev_free(L, d));
+  for (Tile **d : {&L->d_cde_tiles, &L->d_cde_tiles4, &w.d_main, &w.d_seg}) {
+    Tile *old = *d;
+    *d = nullptr;
+    if (old) GG_HIP(dev_free(L, old));
+  }
   w = PipeStrips();
   auto put = [&](const std::vector<Tile> &list, Tile *&d, int &count) -> gg_status {
     if (list.empty()) return GG_OK;
@@ -2911,36 +2952,39 @@ static gg_status cde_tiles(gg_lattice *L) {
     count = (int)list.size();
     return GG_OK;
   };
-  std::vector<Tile> list, seg;
-  gg_status st;
+  std::vector<Tile> list, more, seg;
   L->cde_halo_seg = has_pressure(L);
-  if (L->cde_halo_seg) {
-    build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, list, 1);
-    st = put(list, L->d_cde_tiles, L->n_cde_tiles);
-  } else {
+  build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, list, L->cde_halo_seg ? 1 : 0);
+  gg_status st = put(list, L->d_cde_tiles, L->n_cde_tiles);
+  if (form == CdeForm::tiles4 && st == GG_OK) {
+    build_strips(L, cde_rows4(L), 0, more, 2, TILE4_W);
+    std::stable_sort(more.begin(), more.end(), [&](const Tile &a, const Tile &b) {
+      const int sa = (int)((int64_t)a.x0 * 8 / L->nx), sb = (int)((int64_t)b.x0 * 8 / L->nx);
+      return sa != sb ? sa < sb : (a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0);
+    });
+    st = put(more, L->d_cde_tiles4, L->n_cde_tiles4);
+  } else if (form == CdeForm::walk && st == GG_OK) {
     int cus = 256;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device);
-    // (the halo of a pass wraps once)
     const int axis = std::min(L->p.periodic_x ? L->nx : 8, L->p.periodic_y ? L->ny : 8);
-    w.plan.steps = axis >= 8 ? 8 : axis >= 4 ? 4 : axis >= 2 ? 2 : 0;
-    if (w.plan.steps > 0) {
-      w.plan.rows = cde_walk_rows(pipe_strip_rows(L, CDE_WALK_W), w.plan.steps, 4 * cus);
-      build_pipe(L, w.plan.rows, 0, CDE_WALK_W, w.plan.halo(), list, seg);
-    }
-    st = put(list, w.d_main, w.n_main);
+    w.plan.steps = axis >= 8 ? 8 : 4;
+    w.plan.rows = cde_walk_rows(pipe_strip_rows(L, CDE_WALK_W), w.plan.steps, 4 * cus);
+    build_pipe(L, w.plan.rows, 0, CDE_WALK_W, w.plan.halo(), more, seg);
+    st = put(more, w.d_main, w.n_main);
     if (st == GG_OK) st = put(seg, w.d_seg, w.n_seg);
   }
   if (st != GG_OK) return st;
   L->cde_tiles_rows = L->cde_rows;
+  L->cde_form = form;
   return GG_OK;
 }
 
 // n compound-only steps from a lattice whose counter reads t0 (host mirror),
 // then the counter advances by n. With passes on (cde_rows != 0 and the
 // second plane set present), the steps from an even t go in pairs of passes
-// that end in the first plane set: the walk's, of 8 steps, then of 4, then of
-// 2, or with pressure segments two-step ones; an odd-t first step and the
-// leftover run as single steps.
+// that end in the first plane set: the walk's, of 8 steps, then of 4, or
+// four-step tiles, then two-step tiles; an odd-t first step and the leftover
+// run as single steps.
 static hipError_t launch_cde_steps(gg_lattice *L, int64_t t0, int64_t n, hipStream_t st) {
   hipError_t e = hipSuccess;
   int64_t dt = 0;
@@ -2956,20 +3000,30 @@ static hipError_t launch_cde_steps(gg_lattice *L, int64_t t0, int64_t n, hipStre
         e = launch_rescale(L->storage, L->d_desc, L->d_press, L->n_press, (int)dt, false, st);
       ++dt;
     }
-    const PipeStrips &w = L->cde_walk;
-    for (int steps = w.plan.steps; steps >= 2 && w.n_main + w.n_seg > 0; steps /= 2)
+    auto pairs_of = [&](int steps, auto &&launch) {
       for (; n - dt >= 2 * steps && e == hipSuccess; dt += 2 * steps)
-        for (int k = 0; k < 2 && e == hipSuccess; ++k)
-          e = launch_cde_walk(L->storage, L->pairs, L->d_desc, w.d_seg, w.n_seg, w.d_main, w.n_main, k,
-                              (int)dt + k * steps, steps, st);
-    const int64_t passes = press ? (n - dt) / 4 * 2 : 0;
+        for (int k = 0; k < 2 && e == hipSuccess; ++k) e = launch(k, (int)dt + k * steps);
+    };
+    const PipeStrips &w = L->cde_walk;
+    if (w.n_main + w.n_seg > 0)
+      for (int steps = w.plan.steps; steps >= 4; steps /= 2)
+        pairs_of(steps, [&](int k, int at) {
+          return launch_cde_walk(L->storage, L->pairs, L->d_desc, w.d_seg, w.n_seg, w.d_main, w.n_main,
+                                 k, at, steps, st);
+        });
+    if (L->n_cde_tiles4 > 0)
+      pairs_of(4, [&](int k, int at) {
+        return launch_cde_tile4(L->storage, L->pairs, cde_rows4(L), L->d_desc, L->d_cde_tiles4,
+                                L->n_cde_tiles4, k, at, st);
+      });
+    const int64_t passes = (n - dt) / 4 * 2;
     // (pressure: each pass after the first rescales the state it loads, the
     // kernel the state the last one leaves, in pop_b after dir 0)
     const bool at_load = press && L->cde_halo_seg;
     for (int64_t k = 0; k < passes && e == hipSuccess; ++k) {
       e = launch_cde_tile2(L->storage, L->pairs, L->cde_rows < 0 ? 6 : L->cde_rows, L->d_desc,
                            L->d_cde_tiles, L->n_cde_tiles,
-                           (int)(k & 1) | (at_load && k > 0 ? 2 : 0), (int)(dt + 2 * k), st);
+                           (int)(k & 1) | (at_load && k > 0 ? 2 : 0), (int)(dt + 2 * k), st, press);
       if (e == hipSuccess && press && (!at_load || k == passes - 1))
         e = launch_rescale(L->storage, L->d_desc, L->d_press, L->n_press, (int)(dt + 2 * k + 1),
                            false, st, (k & 1) == 0);
@@ -3069,6 +3123,7 @@ gg_status gg_permute_tiles(gg_lattice *L, uint64_t seed) {
     GG_HIP(shuffle(p.d_seg, p.n_seg));
   }
   GG_HIP(shuffle(L->d_cde_tiles, L->n_cde_tiles));
+  GG_HIP(shuffle(L->d_cde_tiles4, L->n_cde_tiles4));
   GG_HIP(shuffle(L->cde_walk.d_main, L->cde_walk.n_main));
   GG_HIP(shuffle(L->cde_walk.d_seg, L->cde_walk.n_seg));
   gg_drop_cde_graphs(L);

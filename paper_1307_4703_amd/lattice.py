@@ -301,8 +301,8 @@ class Lattice:
 
     def set_cde_launch(self, rows: int = 14) -> None:
         """Passes of up to eight steps for cde_step (rows = 14, 6, -6 or -10:
-        with pressure segments two-step passes over tiles of 14 rows, or 6),
-        or single steps (rows = 0); include/gg.h, gg_set_cde_launch."""
+        the height of the tiles where passes run over tiles), or single steps
+        (rows = 0); include/gg.h, gg_set_cde_launch."""
         A.call("gg_set_cde_launch", self._h, int(rows))
 
     def cde_step(self, n: int = 2) -> None:
