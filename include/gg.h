@@ -477,7 +477,7 @@ typedef struct gg_grads {
  * Device memory: about n/ckpt_every copies of the state plus ckpt_every
  * tape slots of 7 fields; GG_ERR_OOM if it does not fit. Up to 2 GiB of it
  * stay with the lattice for its next run, until that asks for other sizes,
- * the lattice is destroyed, runs of other lattices keep theirs (2 GiB in all)
+ * the lattice is destroyed, runs of other lattices keep theirs (8 GiB in all)
  * or an allocation of the library fails without them (none from a caller's
  * allocator). */
 gg_status gg_adjoint(gg_lattice *lat, int64_t n_steps, int64_t ckpt_every,

@@ -49,9 +49,11 @@ int ilog2(int v) {
 
 // Buffers of adjoint runs that stay with their lattices for the next run
 // (gg_lattice::adjoint_kept), the longest kept first. All lattices of the
-// process together keep at most ADJOINT_KEEP bytes, and an allocation of the
-// library that fails gives them all back and tries again.
-constexpr size_t ADJOINT_KEEP = (size_t)2 << 30;
+// process together keep at most ADJOINT_KEEP_ALL bytes, one at most
+// ADJOINT_KEEP, and an allocation of the library that fails gives them all back
+// and tries again. (Lattices that take turns would otherwise free each other's:
+// three of 1.2 GiB with 2 GiB for all took 9.3 ms a run, 7.5 with 8.)
+constexpr size_t ADJOINT_KEEP = (size_t)2 << 30, ADJOINT_KEEP_ALL = (size_t)8 << 30;
 struct KeptBuffers {
   std::mutex mu;
   std::vector<gg_lattice *> order;
@@ -77,7 +79,7 @@ struct KeptBuffers {
     order.push_back(L);
     size_t total = 0;
     for (const gg_lattice *q : order) total += bytes(q);
-    while (total > ADJOINT_KEEP) {
+    while (total > ADJOINT_KEEP_ALL) {
       total -= bytes(order.front());
       release(order.front());
       order.erase(order.begin());
@@ -2930,21 +2932,23 @@ static CdeForm cde_form(const gg_lattice *L) {
 static int cde_rows4(const gg_lattice *L) { return L->cde_rows < 0 ? -L->cde_rows : 6; }
 
 // Work lists of the compound-only passes for the row count and form in force:
-// two-step tiles and, by the form, four-step tiles (in eight vertical stripes,
+// two-step tiles (with pairs: some run ends in them) and, by the form, four-step tiles (in eight vertical stripes,
 // each walked band by band: an XCD takes a contiguous run of the list) or the
 // walk's strips.
-static gg_status cde_tiles(gg_lattice *L) {
+static gg_status cde_tiles(gg_lattice *L, bool pairs) {
   const CdeForm form = cde_form(L);
-  if (L->cde_rows == 0 || (L->cde_tiles_rows == L->cde_rows && L->cde_form == form)) return GG_OK;
-  gg_drop_cde_graphs(L);
-  L->n_cde_tiles = L->n_cde_tiles4 = L->cde_tiles_rows = 0;
+  if (L->cde_rows == 0) return GG_OK;
   PipeStrips &w = L->cde_walk;
-  for (Tile **d : {&L->d_cde_tiles, &L->d_cde_tiles4, &w.d_main, &w.d_seg}) {
-    Tile *old = *d;
-    *d = nullptr;
-    if (old) GG_HIP(dev_free(L, old));
+  if (L->cde_tiles_rows != L->cde_rows || L->cde_form != form) {
+    gg_drop_cde_graphs(L);
+    L->n_cde_tiles = L->n_cde_tiles4 = L->cde_tiles_rows = 0;
+    Tile *old[4] = {L->d_cde_tiles, L->d_cde_tiles4, w.d_main, w.d_seg};
+    L->d_cde_tiles = L->d_cde_tiles4 = nullptr;
+    w = PipeStrips();
+    L->cde_halo_seg = has_pressure(L);
+    for (Tile *d : old)
+      if (d) GG_HIP(dev_free(L, d));
   }
-  w = PipeStrips();
   auto put = [&](const std::vector<Tile> &list, Tile *&d, int &count) -> gg_status {
     if (list.empty()) return GG_OK;
     GG_HIP(dev_alloc(L, (void **)&d, list.size() * sizeof(Tile)));
@@ -2952,18 +2956,22 @@ static gg_status cde_tiles(gg_lattice *L) {
     count = (int)list.size();
     return GG_OK;
   };
-  std::vector<Tile> list, more, seg;
-  L->cde_halo_seg = has_pressure(L);
-  build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, list, L->cde_halo_seg ? 1 : 0);
-  gg_status st = put(list, L->d_cde_tiles, L->n_cde_tiles);
-  if (form == CdeForm::tiles4 && st == GG_OK) {
+  gg_status st = GG_OK;
+  if ((pairs || form == CdeForm::tiles2) && L->n_cde_tiles == 0) {
+    std::vector<Tile> list;
+    build_strips(L, L->cde_rows < 0 ? 6 : L->cde_rows, 0, list, L->cde_halo_seg ? 1 : 0);
+    st = put(list, L->d_cde_tiles, L->n_cde_tiles);
+  }
+  if (st != GG_OK || L->cde_tiles_rows == L->cde_rows) return st;
+  std::vector<Tile> more, seg;
+  if (form == CdeForm::tiles4) {
     build_strips(L, cde_rows4(L), 0, more, 2, TILE4_W);
     std::stable_sort(more.begin(), more.end(), [&](const Tile &a, const Tile &b) {
       const int sa = (int)((int64_t)a.x0 * 8 / L->nx), sb = (int)((int64_t)b.x0 * 8 / L->nx);
       return sa != sb ? sa < sb : (a.y0 != b.y0 ? a.y0 < b.y0 : a.x0 < b.x0);
     });
     st = put(more, L->d_cde_tiles4, L->n_cde_tiles4);
-  } else if (form == CdeForm::walk && st == GG_OK) {
+  } else if (form == CdeForm::walk) {
     int cus = 256;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, L->device);
     const int axis = std::min(L->p.periodic_x ? L->nx : 8, L->p.periodic_y ? L->ny : 8);
@@ -3016,7 +3024,7 @@ static hipError_t launch_cde_steps(gg_lattice *L, int64_t t0, int64_t n, hipStre
         return launch_cde_tile4(L->storage, L->pairs, cde_rows4(L), L->d_desc, L->d_cde_tiles4,
                                 L->n_cde_tiles4, k, at, st);
       });
-    const int64_t passes = (n - dt) / 4 * 2;
+    const int64_t passes = L->n_cde_tiles > 0 ? (n - dt) / 4 * 2 : 0;
     // (pressure: each pass after the first rescales the state it loads, the
     // kernel the state the last one leaves, in pop_b after dir 0)
     const bool at_load = press && L->cde_halo_seg;
@@ -3058,12 +3066,15 @@ gg_status gg_cde_step(gg_lattice *L, int64_t n) {
       return fail(GG_ERR_STATE, "velocity field slot " + std::to_string(s) + " of phase " +
                                     std::to_string(k) + " was never set");
   }
-  if ((st = pressure_nodes(L)) != GG_OK || (st = cde_tiles(L)) != GG_OK ||
-      (st = wall_nodes(L)) != GG_OK)
-    return st;
   int64_t left = n;
   const int K = L->graph_chunk;  // even
   const int par = (int)(L->t & 1);
+  // does a replayed chunk or the rest end in a pair of two-step passes
+  auto ends_in_pairs = [&](int64_t m) { return m > par && (m - par) % 8 >= 4; };
+  const bool pairs = K > 0 && n >= K ? ends_in_pairs(K) || ends_in_pairs(n % K) : ends_in_pairs(n);
+  if ((st = pressure_nodes(L)) != GG_OK || (st = cde_tiles(L, pairs)) != GG_OK ||
+      (st = wall_nodes(L)) != GG_OK)
+    return st;
   if (K > 0 && left >= K) {
     if (!L->cde_exec[par]) {
       GG_HIP(hipStreamBeginCapture(L->cap_stream, hipStreamCaptureModeThreadLocal));

@@ -25,16 +25,16 @@ def _gradient(lat, wl, n=400):
     return lat.adjoint(n, weight, target, r_box=r_box)
 
 
-def test_lattices_together_keep_two_gib():
+def test_lattices_together_keep_eight_gib():
     """Each run of 400 steps takes more than a GiB of checkpoints and tapes."""
     wl = W.gradient_generator(nx=1024, ny=512, half_period=150, storage="f32")
-    lats = [Lattice.from_workload(wl) for _ in range(4)]
+    lats = [Lattice.from_workload(wl) for _ in range(10)]
     base = _used()
     for k, lat in enumerate(lats):
         log(f"adjoint of lattice {k}")
         _gradient(lat, wl)
     kept = _used() - base
-    assert kept < 2.25 * GIB
+    assert 2 * GIB < kept < 8.25 * GIB
     for lat in lats:
         lat.close()
     assert _used() <= base
