@@ -84,6 +84,7 @@ class Lattice:
         self.mask = np.ascontiguousarray(mask, dtype=np.uint8)
         self.ny, self.nx = self.mask.shape
         self.storage = storage
+        self.periodic = (bool(periodic[0]), bool(periodic[1]))
         self.D = float(D)
         p = A.gg_params(float(tau_f), float(D), float(w0), float(rho0),
                         float(k_decay), float(c_shift), int(bool(periodic[0])),
@@ -148,6 +149,7 @@ class Lattice:
         k = {"inlet": A.GG_SEG_INLET, "outlet": A.GG_SEG_OUTLET}[kind]
         A.call("gg_set_segment", self._h, int(sid), k, int(normal[0]),
                int(normal[1]), float(u_max), float(c_in))
+        self.segments.pop(int(sid), None)
 
     def set_schedule(self, schedule: Optional[Sequence], t_origin: int = 0) -> None:
         if not schedule:

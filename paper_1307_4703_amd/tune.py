@@ -7,17 +7,19 @@ kernel) and the pipelined passes, for batches persistent grid sizes, and for
 the compound-only step passes or single steps. Each candidate is timed
 on the GPU with HIP events over a few graph-replayed steps (the lattices
 advance while being tuned, so tune before the run or on a copy). Results are cached in a JSON
-file keyed by the device name, storage type and the lattices' shapes and
-fluid counts.
+file keyed by the device name, the built library, and what the forms depend on
+of each lattice: shape, fluid count, storage type, layout, periodic axes and
+whether it has pressure segments.
 """
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import os
 from typing import Dict, Iterable, List, Optional, Sequence, Tuple
 
-from ._abi import GGError
+from ._abi import LIB_PATH, GGError
 
 TILES: Tuple[Tuple[int, int], ...] = ((64, 4), (32, 8), (64, 2), (128, 2), (128, 1),
                                       (64, 8), (128, 4), (256, 1), (32, 4), (16, 8))
@@ -32,11 +34,23 @@ def cache_path() -> str:
     return os.path.join(base, "paper_1307_4703_amd", "tune.json")
 
 
+@functools.lru_cache(maxsize=None)
+def _library(path: str = LIB_PATH) -> str:
+    """Digest of the built library: what one build's kernels were timed at says
+    nothing about another's."""
+    try:
+        with open(path, "rb") as fh:
+            return hashlib.sha256(fh.read()).hexdigest()[:16]
+    except OSError:
+        return "none"
+
+
 def _key(lattices: Sequence, kind: str) -> str:
     import torch
     dev = torch.cuda.get_device_name(0) if torch.cuda.is_available() else "none"
-    desc = [(l.nx, l.ny, l.storage, l.info()["n_fluid"]) for l in lattices]
-    h = hashlib.sha256(json.dumps([dev, kind, desc]).encode()).hexdigest()[:20]
+    desc = [(l.nx, l.ny, l.storage, l.info()["n_fluid"], l.layout, list(l.periodic),
+             any(s[0] == "pressure" for s in l.segments.values())) for l in lattices]
+    h = hashlib.sha256(json.dumps([dev, _library(), kind, desc]).encode()).hexdigest()[:20]
     return f"{kind}:{h}"
 
 
