@@ -423,9 +423,11 @@ static void build_pipe(const gg_lattice *L, int h, int inst, int width, int halo
         if (!L->p.periodic_y) continue;
         yy = (yy + ny) % ny;
       }
-      for (int x : touch[yy])
-        for (int wrap = L->p.periodic_x ? -1 : 0; wrap <= (L->p.periodic_x ? 1 : 0); ++wrap)
-          if (x + wrap * nx >= x0 - halo && x + wrap * nx <= x0 + width - 1 + halo) return true;
+      const std::vector<int> &t = touch[yy];  // (in order)
+      for (int wrap = L->p.periodic_x ? -1 : 0; wrap <= (L->p.periodic_x ? 1 : 0); ++wrap) {
+        const auto it = std::lower_bound(t.begin(), t.end(), x0 - halo - wrap * nx);
+        if (it != t.end() && *it <= x0 + width - 1 + halo - wrap * nx) return true;
+      }
     }
     return false;
   };
