@@ -9,10 +9,10 @@ namespace gg {
 // (64, 128, 256 or 512), tile width 1 << tx_shift, odd = parity of the
 // step, dt added to the device step counter of each lattice. persist > 0
 // caps the grid at that many work-groups (rounded up to a multiple of 8),
-// which then stride through the tiles.
+// which then stride through the tiles. press: the lattice has pressure segments.
 hipError_t launch_step(gg_storage s, bool pairs, int block, bool odd, const LatDesc *d,
                        const Tile *tiles, int n_tiles, int tx_shift, int dt, hipStream_t st,
-                       int persist = 0);
+                       int persist = 0, bool press = false);
 // launch_step that also writes, for each fluid node, the state before the
 // step to `tape` (compute type, plane stride of the populations: dg_0..4,
 // u_x, u_y), the adjoint's tape.

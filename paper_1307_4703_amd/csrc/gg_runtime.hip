@@ -1461,7 +1461,7 @@ static hipError_t launch_steps(gg_lattice *L, int64_t t0, int64_t n, hipStream_t
       if (e == hipSuccess) e = prof_begin(L, st, pidx);
       if (e == hipSuccess)
         e = launch_step(L->storage, L->pairs, block, ((t0 + dt) & 1) != 0, L->d_desc,
-                        L->d_tiles, L->n_tiles, txs, (int)dt, st);
+                        L->d_tiles, L->n_tiles, txs, (int)dt, st, 0, L->n_press > 0);
       if (e == hipSuccess) e = prof_end(L, st, pidx, 1 + (int)((t0 + dt) & 1));
       if (e == hipSuccess && L->n_wall > 0)
         e = launch_wall_apply(L->storage, L->d_desc, L->d_wall_links, L->n_wall_links,
