@@ -72,8 +72,10 @@ def workload(name):
     return table[name]()
 
 
-# launch form per workload ((fuse, rows) of gg_set_two_step), as the
-# autotuner picks it on this GPU; --tune re-runs the autotuner
+# launch form per workload ((fuse, rows) of gg_set_two_step); --tune asks the
+# autotuner instead. The FP16 lattices stay in two-step passes, where their
+# earlier lines were taken; fuse 5 is faster on them (us a step: gg8192_f16 61.5
+# and 41.2, allfluid8192_f16 235 and 146, gg2048_f16 7.0 and 6.7)
 FORMS = {"gg2048_f32": (5, 6), "gg2048_f16": (4, 6), "gg8192_f16": (3, 6),
          "gg8192_f16_pe2000": (3, 6), "gg8192_f32": (5, 6), "allfluid8192_f32": (5, 6),
          "allfluid8192_f16": (3, 6), "shard8192x512_f32": (5, 6),

@@ -290,9 +290,11 @@ gg_status gg_set_launch(gg_lattice *lat, int32_t tile_x, int32_t tile_y,
  *     first step's row-crossing populations exchanged through LDS;
  *   fuse = 4: the tiles of fuse = 3, with the boundary-segment rules
  *     compiled into the one kernel that does every tile (with 2 and 3 the
- *     strips and tiles that touch a segment run in a kernel of their own,
- *     beside the others on a second stream, which keeps the boundary code
- *     out of the others' register budget);
+ *     rows that touch a segment run in tiles of two rows in a kernel of
+ *     their own, beside the others on a second stream, which keeps the
+ *     boundary code out of the others' register budget; small lattices
+ *     without pressure segments take the one kernel with 3 too, where the
+ *     second launch costs more than that);
  *   fuse = 5: runs of 4k steps from an even step in pairs of passes of four
  *     steps, or, for FP32 lattices beyond the Infinity Cache (from 2M fluid
  *     nodes), of eight (temporal blocking over the AA pairs of steps,
@@ -303,12 +305,13 @@ gg_status gg_set_launch(gg_lattice *lat, int32_t tile_x, int32_t tile_y,
  *     rows from LDS; the library picks the strips' height, and whether the
  *     strips that link to a segment run in the one kernel with the others
  *     (small lattices) or in a kernel of their own on the second stream.
- *     The smallest lattices (up to 1024 tiles) take their four steps over
- *     tiles of 58 columns x 6 rows, all rows at once. Other runs, and mostly
- *     the last four steps of a run, step as with fuse = 3 (strip_h 6 or 14). Lattices without
- *     pressure segments or the paper's walls, periodic axes of 4 nodes or
- *     more; otherwise fuse = 5 steps as fuse = 3. The
- *     result is that of single steps, bit for bit, as for every form.
+ *     The smallest lattices (up to 1024 tiles, 768 in FP64) take their four
+ *     steps over tiles of 58 columns x 6 rows, all rows at once. Other runs,
+ *     and mostly the last four steps of a run, step as with fuse = 3
+ *     (strip_h 6 or 14). Lattices without pressure segments or the paper's
+ *     walls, periodic axes of 4 nodes or more; otherwise fuse = 5 steps as
+ *     fuse = 3. The result is that of single steps, bit for bit, as for
+ *     every form.
  * Each collides a one-node halo around its strip or tile once more for the
  * first step. Errors: GG_ERR_ARG for other values, and for fuse = 2 where
  * two vertically adjacent fluid nodes link to more than two boundary
@@ -441,12 +444,14 @@ gg_status gg_batch_form(const gg_batch *batch, int32_t *tile_x, int32_t *tile_y,
 /* Two-step pass for the batch (see gg_set_two_step): fuse 3 or 4 with
  * tiles of rows = 6 or 14 rows, over the members' tiles in one flat list
  * (fuse 3: the boundary tiles of all members in a second list on a second
- * stream); fuse 5: passes of four or eight steps over the members' strips
- * (chosen for the members' fluid nodes together), GG_ERR_ARG for a member
- * with a periodic axis under 4 nodes; fuse = 1 goes back to single steps. Every member must have its
- * second plane set (fuse >= 2 on the member, the default) and all members
- * must sit at steps of one parity (else GG_ERR_STATE). The states advance
- * exactly as with single steps. */
+ * stream, or, where the members are few tiles together, in the one kernel);
+ * fuse 5: passes of four or eight steps over the members' strips or, for
+ * the smallest, four-step tiles (chosen for the members' fluid nodes
+ * together), GG_ERR_ARG for a member with a periodic axis under 4 nodes;
+ * fuse = 1 goes back to single steps. Every member must have its second
+ * plane set (fuse >= 2 on the member, the default) and all members must sit
+ * at steps of one parity (else GG_ERR_STATE). The states advance exactly as
+ * with single steps. */
 gg_status gg_batch_set_two_step(gg_batch *batch, int32_t fuse, int32_t rows);
 gg_status gg_batch_info(const gg_batch *batch, int64_t *n_tiles, int64_t *n_fluid);
 void gg_batch_destroy(gg_batch *batch);
@@ -565,11 +570,11 @@ gg_status gg_monitor_read(gg_lattice *lat, gg_diag *out, int64_t *count);
 /* Result of gg_step_profile. The dominant kernel is the one that takes the
  * most HBM traffic: the kernel over the interior tile list of each two-step
  * pass (with fuse 2 and 3 the boundary tiles run in a second kernel beside
- * it on a side stream; with fuse 4 it is the pass's only kernel), of each
- * pass of four or eight steps where fuse 5 runs them (one kernel, or on
- * large lattices with its boundary strips' kernel beside it; the shorter
- * passes of leftover steps are then counted apart, in n_pass2), or the step kernel of each single
- * step. */
+ * it on a side stream, but for small lattices; with fuse 4 it is the pass's
+ * only kernel), of each pass of four or eight steps where fuse 5 runs them
+ * (one kernel, or on large lattices with its boundary strips' kernel beside
+ * it; the shorter passes of leftover steps are then counted apart, in
+ * n_pass2), or the step kernel of each single step. */
 typedef struct gg_profile {
   double ms_total;          /* HIP events around the whole call */
   int64_t n_pass;           /* plain launches of the pass's dominant kernel */
@@ -598,7 +603,8 @@ typedef struct gg_profile {
   int32_t steps_per_pass;   /* 2, or 4 or 8 where fuse 5's passes run (their
                                strips are then the pass_ fields' tiles, one
                                work-group of steps_per_pass wavefronts each,
-                               and rows the strips' height) */
+                               and rows the strips' height; over four-step
+                               tiles, rows 6, rows + 6 wavefronts each) */
 } gg_profile;
 
 /* Instrumentation: gg_step(lat, n) with a pair of HIP events recorded on

@@ -745,8 +745,7 @@ __device__ __forceinline__ void cde_walk_strip(CDesc &L, const GG_CONST Tile &tl
 // Us a step, planes: 8192 x 4096 all fluid FP32 56-65 (two- and four-step
 // tiles in LDS: 210 and 199), FP64 104 (337, 269), FP16 50 (167, 189); 2048 x
 // 1024 gradient generator FP32 2.5 (5.5); 8192 x 4096 FP16 16 (48, single
-// steps 46); 410 x 205 with four segments 2.3 (3.1), where the strips next to
-// segments are the last to end.
+// steps 46). Where the walk runs and where the tiles: the runtime's cde_form.
 template <class S, int NS, bool SEG, bool PAIRS>
 __global__ void __launch_bounds__(64, NS < 8 ? 1 : sizeof(typename Pop<S>::T) == 8 ? 2 : SEG ? 3 : 4)
     k_cde_walk(const LatDesc *__restrict__ desc, const Tile *__restrict__ seg_tiles, int n_seg,

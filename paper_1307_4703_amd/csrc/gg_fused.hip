@@ -217,6 +217,8 @@ __global__ void __launch_bounds__(256)
 // Wavefronts a SIMD must hold in the boundary tiles' kernel: with 80 registers
 // three work-groups of 6-row tiles fit a CU in FP32, two with a few more (2048
 // x 1024 gradient generator in one kernel, 64 steps: 540 us, and 580 with 86).
+// With pressure segments 96 registers: two work-groups of 6-row tiles (as with
+// 128) and five of the 2-row tiles beside the others (four).
 constexpr int tile2_waves(bool seg, bool press, size_t bytes) {
   return !seg ? 1 : bytes == 8 ? (press ? 3 : 4) : press ? 5 : 6;
 }

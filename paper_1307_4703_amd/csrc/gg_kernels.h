@@ -80,7 +80,7 @@ hipError_t launch_cde_tile2(gg_storage s, bool pairs, int rows, const LatDesc *d
 // rows, rows 6 or 10; dir and dt as for launch_tile2.
 hipError_t launch_cde_tile4(gg_storage s, bool pairs, int rows, const LatDesc *d,
                             const Tile *tiles, int n_tiles, int dir, int dt, hipStream_t st);
-// Compound-only passes of `steps` (2, 4 or 8) steps (t even, no pressure
+// Compound-only passes of `steps` (4 or 8) steps (t even, no pressure
 // segments): one wavefront per strip of CDE_WALK_W columns x (flags >> 8)
 // rows, the segment strips (seg_tiles) first; dir and dt as for launch_tile2.
 constexpr int CDE_WALK_W = 50;

@@ -533,7 +533,8 @@ static int64_t pipe_strip_rows(const gg_lattice *L, int width) {
 // 2048 x 1024 gradient generator FP32 5.9-6.0 us a step with 10..14 rows, 6.3
 // with 16, FP64 8.5 with 14 (one round) and 10.4 with 12 (two); 6144 x 3072
 // FP32 29.3 with 48 rows (2.3 rounds), 38.5 with 128 (0.9); 8192 x 4096
-// all-fluid 152 with 96 and 128, 164 with 48.
+// all-fluid 152 with 96 and 128, 164 with 48. Fewer than 8 rows would be for
+// lattices that take four-step tiles instead (tile4_tiles).
 static int pipe_pick_rows(int64_t strip_rows, int steps, int slots, int cus, bool cached) {
   int best = 16;
   double best_cost = 0.0;
@@ -611,9 +612,10 @@ static int64_t owned_fluid(const gg_lattice *L, const std::vector<Tile> &list, i
 
 static bool has_pressure(const gg_lattice *L);
 
-// The four-step pass (fuse 5) covers this lattice: no pressure segments
-// (their rescaling runs between steps) nor the paper's walls, and periodic
-// axes of 4 nodes or more (the tiles' three-node halo wraps once).
+// The passes of four and eight steps (fuse 5) cover this lattice: no pressure
+// segments (their rescaling runs between steps) nor the paper's walls, and
+// periodic axes of 4 nodes or more (the tiles' three-node halo wraps once; the
+// strips of eight steps ask for their own halo, in pipe_plan).
 static bool pass4_ok(const gg_lattice *L) {
   return L->fuse == 5 && !has_pressure(L) && L->wall_scheme == 0 &&
          (!L->p.periodic_x || L->nx >= 4) && (!L->p.periodic_y || L->ny >= 4);
@@ -1385,8 +1387,8 @@ static hipError_t launch_pass(gg_lattice *L, int dir, int dt, hipStream_t st) {
   const bool fork = L->n_seg_strips > 0 && L->n_strips > 0;
   const bool press = L->n_press > 0;  // (fuse 3, 4 and 5 only)
   long pidx = -1;
-  // (with the four-step pass on, the two-step passes of leftover steps are
-  // not the dominant kernel: profiled apart, kind 4)
+  // (with passes of four or eight steps on, the two-step passes of leftover
+  // steps are not the dominant kernel: profiled apart, kind 4)
   const int kind = L->tiles4 && pass4_ok(L) ? 4 : 0;
   if (one_kernel(L)) {
     e = prof_begin(L, st, pidx);
@@ -2934,9 +2936,9 @@ static CdeForm cde_form(const gg_lattice *L) {
 static int cde_rows4(const gg_lattice *L) { return L->cde_rows < 0 ? -L->cde_rows : 6; }
 
 // Work lists of the compound-only passes for the row count and form in force:
-// two-step tiles (with pairs: some run ends in them) and, by the form, four-step tiles (in eight vertical stripes,
-// each walked band by band: an XCD takes a contiguous run of the list) or the
-// walk's strips.
+// two-step tiles (with pairs: some run ends in them) and, by the form, four-step
+// tiles (in eight vertical stripes, each walked band by band: an XCD takes a
+// contiguous run of the list) or the walk's strips.
 static gg_status cde_tiles(gg_lattice *L, bool pairs) {
   const CdeForm form = cde_form(L);
   if (L->cde_rows == 0) return GG_OK;
@@ -3111,7 +3113,7 @@ gg_status gg_set_wall_scheme(gg_lattice *L, int32_t scheme) {
   GG_HIP(hipStreamSynchronize(L->stream));
   L->wall_scheme = scheme;
   L->wall_dirty = true;
-  // (the four-step pass's lists follow the wall scheme)
+  // (the lists of the passes of four and eight steps follow the wall scheme)
   return L->tiles4 != pass4_ok(L) ? gg_rebuild_tiles(L) : GG_OK;
 }
 

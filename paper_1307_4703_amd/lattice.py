@@ -189,10 +189,10 @@ class Lattice:
     def set_two_step(self, fuse: int = 3, strip_h: int = 6) -> None:
         """Two steps per pass over memory (fuse = 2: walking strips of
         strip_h rows; 3, the default: row-parallel tiles of 6 or 14 rows with
-        the boundary kernel apart; 4: the same in one kernel), four or eight
-        steps per pass in runs of 4k steps (fuse = 5; other runs as fuse = 3)
-        or single steps (fuse = 1); include/gg.h,
-        gg_set_two_step."""
+        the boundary kernel apart where the lattice is not small; 4: the same
+        in one kernel), four or eight steps per pass in runs of 4k steps
+        (fuse = 5; other runs as fuse = 3) or single steps (fuse = 1);
+        include/gg.h, gg_set_two_step."""
         A.call("gg_set_two_step", self._h, int(fuse), int(strip_h))
 
     def set_layout(self, layout: str) -> None:
