@@ -444,10 +444,9 @@ gg_status gg_batch_form(const gg_batch *batch, int32_t *tile_x, int32_t *tile_y,
 /* Two-step pass for the batch (see gg_set_two_step): fuse 3 or 4 with
  * tiles of rows = 6 or 14 rows, over the members' tiles in one flat list
  * (fuse 3: the boundary tiles of all members in a second list on a second
- * stream, or, where the members are few tiles together, in the one kernel);
- * fuse 5: passes of four or eight steps over the members' strips or, for
- * the smallest, four-step tiles (chosen for the members' fluid nodes
- * together), GG_ERR_ARG for a member with a periodic axis under 4 nodes;
+ * stream); fuse 5: passes of four or eight steps over the members' strips
+ * or, for the smallest, four-step tiles (chosen for the members together),
+ * GG_ERR_ARG for a member with a periodic axis under 4 nodes;
  * fuse = 1 goes back to single steps. Every member must have its second
  * plane set (fuse >= 2 on the member, the default) and all members must sit
  * at steps of one parity (else GG_ERR_STATE). The states advance exactly as
