@@ -165,8 +165,9 @@ def tune_cde(lat, steps: int = 256, rows: Iterable[int] = (0, 6, 14, -6, -10),
              path: Optional[str] = None) -> Dict:
     """Pick the launch form of the compound-only step (passes or single
     steps; the rows are those of the two- and four-step tiles, where the
-    lattice takes tiles) with the shortest step time and apply it. Needs a velocity field for every phase;
-    advances the compound (steps should be a multiple of 16)."""
+    lattice takes tiles) with the shortest step time and apply it. Needs a
+    velocity field for every phase; advances the compound (steps should be a
+    multiple of 16)."""
     path = path or cache_path()
     key = _key([lat], "cde4")
     if use_cache:
